@@ -14,12 +14,19 @@
 #include "march.hpp"
 
 namespace dugks {
-long long batch_resident_slots(int lattice, int dtype, bool uniform, int variant, int n_cu);
-hipError_t batch_step_launch(int lattice, int dtype, bool uniform, int variant, const void* insts,
-                             const long long* bstart, const BatchGeom* geom, int n, long long nblocks, const void* fin,
-                             const void* forces, void* fout, const long long* step0, int step, hipStream_t st);
-int fused_tile_variants(int lattice);
-void fused_tile_shape(int lattice, int variant, int* bx, int* by);
+long long batch_resident_slots(int dtype, bool uniform, int n_cu);
+hipError_t batch_step_launch(int dtype, bool uniform, const void* insts, const long long* bstart,
+                             const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
+                             void* fout, const long long* step0, int step, hipStream_t st);
+void fused_tile_shape(int* bx, int* by);
+// the D2Q9 tile kernel
+long long tile_count(int nx, int ny, int steps);
+int tile_batch_steps(int dtype, int n, const int* nx, const int* ny, int n_cu);
+std::vector<int> tile_plan(int nsteps, int most);
+void tile_blocks(int inst, int nx, int ny, int steps, std::vector<TileBlock>& out);
+hipError_t tile_batch_launch(int dtype, const void* insts, const TileBlock* blocks, long long nblocks,
+                             const void* fin, const void* forces, void* fout, const long long* step0, int step,
+                             int steps, hipStream_t st);
 
 // batch clock: set (reset != 0: s = add) or advance (s += add) the
 // device-side step counter (kernel nodes, so a captured run replays them)
@@ -51,7 +58,10 @@ using namespace dugks;
 
 struct dugks_batch {
     int n = 0, lattice = 0, dtype = 0, D = 0, Q = 0, esize = 0;
-    int tile = 0, chunk = 0;  // tile-shape variant and march chunk (0 = default) in use
+    int chunk = 0;            // march chunk in use (0 = default)
+    int most = 1, model = 1;  // D2Q9: time steps of one launch, and the model's choice
+    TileBlock* tiles_dev[TILE_MAX_STEPS + 1] = {};  // D2Q9: the workgroups of a launch of s steps
+    long long tblocks[TILE_MAX_STEPS + 1] = {};  // D2Q9: workgroups of a launch of s steps
     bool uniform = true;      // every instance on a uniform mesh
     bool any_field = false;   // some instance has a force field
     std::vector<dugks_config> cfgs;
@@ -96,27 +106,73 @@ void fill_inst(const dugks_config* c, Inst<T>& P, T* met_dev, std::vector<T>& me
 size_t metric_len(const dugks_config* c);
 }  // namespace dugks
 
-// Workgroup geometry of every instance for tile-shape variant `tile` and
-// march chunk `chunk`: tile counts, chunk and the workgroup prefix sum;
+static int device_cus()
+{
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        ncu = 0;
+    return ncu;
+}
+
+// D2Q9: the workgroups of a launch of `steps` steps per instance, uploaded
+// when they change (synchronously, never inside a capture)
+static int set_tiles(dugks_batch* b, int steps)
+{
+    if (b->tiles_dev[steps]) return DUGKS_OK;
+    std::vector<TileBlock> blocks;
+    for (int i = 0; i < b->n; ++i) tile_blocks(i, b->cfgs[i].n[0], b->cfgs[i].n[1], steps, blocks);
+    if (hipMalloc((void**)&b->tiles_dev[steps], sizeof(TileBlock) * blocks.size()) != hipSuccess)
+        return bfail(b, DUGKS_ENOMEM, "batch table allocation");
+    if (hipMemcpy(b->tiles_dev[steps], blocks.data(), sizeof(TileBlock) * blocks.size(), hipMemcpyHostToDevice) != hipSuccess)
+        return bfail(b, DUGKS_EHIP, "batch geometry upload");
+    return DUGKS_OK;
+}
+
+// the D2Q9 launches of the batch take up to `most` steps each
+static int set_most(dugks_batch* b, int most)
+{
+    for (int s = 1; s <= most; ++s) {
+        const int rc = set_tiles(b, s);
+        if (rc != DUGKS_OK) return rc;
+    }
+    b->most = most;
+    return DUGKS_OK;
+}
+
+// workgroups of a launch of `steps` steps, and the model's choice of `most`
+static int choose_most(dugks_batch* b)
+{
+    std::vector<int> nx(b->n), ny(b->n);
+    for (int i = 0; i < b->n; ++i) {
+        nx[i] = b->cfgs[i].n[0];
+        ny[i] = b->cfgs[i].n[1];
+    }
+    for (int s = 1; s <= TILE_MAX_STEPS; ++s) {
+        b->tblocks[s] = 0;
+        for (int i = 0; i < b->n; ++i) b->tblocks[s] += tile_count(nx[i], ny[i], s);
+    }
+    // (a table of workgroups also has to fit the host's memory)
+    if (b->tblocks[1] > (1LL << 26)) return bfail(b, DUGKS_EUNSUPPORTED, "batch too large for one launch");
+    b->model = tile_batch_steps(b->dtype, b->n, nx.data(), ny.data(), device_cus());
+    while (b->tblocks[b->model] > (1LL << 26)) --b->model;
+    return set_most(b, b->model);
+}
+
+// D3Q19: workgroup geometry of every instance for march chunk `chunk`: tile counts, chunk and the workgroup prefix sum;
 // uploaded synchronously (never inside a capture).  chunk > 0: the same chunk
 // for every instance; chunk = 0: a chunk per instance from the chunk model
 // (auto_chunk) with the device's resident workgroups shared among the
 // instances in proportion to their cells, so that large instances march
 // long chunks (fewer recomputed halo planes) and small ones short chunks
 // (more workgroups at once).
-static int set_geometry(dugks_batch* b, int tile, int chunk)
+static int set_geometry(dugks_batch* b, int chunk)
 {
     const int n = b->n, D = b->D, M = D - 1;
     int bx, by;
-    fused_tile_shape(b->lattice, tile, &bx, &by);
+    fused_tile_shape(&bx, &by);
     long long slots = 0;
-    if (chunk == 0) {
-        int dev = 0, ncu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            ncu = 0;
-        slots = batch_resident_slots(b->lattice, b->dtype, b->uniform, tile, ncu);
-    }
+    if (chunk == 0) slots = batch_resident_slots(b->dtype, b->uniform, device_cus());
     std::vector<long long> bstart(n + 1, 0);
     std::vector<BatchGeom> geom(n);
     for (int i = 0; i < n; ++i) {
@@ -143,7 +199,6 @@ static int set_geometry(dugks_batch* b, int tile, int chunk)
         return bfail(b, DUGKS_EHIP, "batch geometry upload");
     drop_graph(b);
     b->nblocks = bstart[n];
-    b->tile = tile;
     b->chunk = chunk;
     return DUGKS_OK;
 }
@@ -183,7 +238,7 @@ static int build_tables(dugks_batch* b, const int64_t* offsets, hipStream_t st)
         hipMemcpy(b->cstart_dev, cstart.data(), sizeof(long long) * (n + 1), hipMemcpyHostToDevice) != hipSuccess)
         return bfail(b, DUGKS_EHIP, "batch table upload");
     (void)st;
-    return set_geometry(b, 0, 0);
+    return b->D == 2 ? choose_most(b) : set_geometry(b, 0);
 }
 
 extern "C" int dugks_batch_create(const dugks_config* cfgs, int n, const int64_t* offsets, void* stream,
@@ -254,22 +309,30 @@ extern "C" int dugks_batch_init(dugks_batch* b, void* f_out, void* stream)
     return b->dtype == DUGKS_F64 ? batch_init_t<D3Q19, double>(b, f_out, st) : batch_init_t<D3Q19, float>(b, f_out, st);
 }
 
-static int batch_launch_any(dugks_batch* b, const void* fin, void* fout, const void* forces, int step, hipStream_t st)
+static int batch_launch_any(dugks_batch* b, const void* fin, void* fout, const void* forces, int step, int steps,
+                            hipStream_t st)
 {
     // without any field the field-free kernels run (as for single instances)
     const void* fz = b->any_field ? forces : nullptr;
-    const hipError_t e = batch_step_launch(b->lattice, b->dtype, b->uniform, b->tile, b->insts_dev, b->bstart_dev,
-                                           b->geom_dev, b->n, b->nblocks, fin, fz, fout, b->step_dev, step, st);
+    const hipError_t e =
+        b->D == 2 ? tile_batch_launch(b->dtype, b->insts_dev, b->tiles_dev[steps], b->tblocks[steps], fin, fz, fout,
+                                      b->step_dev, step, steps, st)
+                  : batch_step_launch(b->dtype, b->uniform, b->insts_dev, b->bstart_dev, b->geom_dev, b->n,
+                                      b->nblocks, fin, fz, fout, b->step_dev, step, st);
     return e == hipSuccess ? DUGKS_OK : bfail(b, DUGKS_EHIP, hipGetErrorString(e));
 }
 
-static int launch_run(dugks_batch* b, const void* f_in, void* f_out, const void* forces, int nsteps, hipStream_t st)
+// the launches of `plan` (steps of each), then the clock
+static int launch_plan(dugks_batch* b, const void* f_in, void* f_out, const void* forces, const std::vector<int>& plan,
+                       hipStream_t st)
 {
     const void* cur = f_in;
     void* nxt = f_out;
-    for (int k = 0; k < nsteps; ++k) {
-        const int rc = batch_launch_any(b, cur, nxt, forces, k, st);
+    int nsteps = 0;
+    for (const int s : plan) {
+        const int rc = batch_launch_any(b, cur, nxt, forces, nsteps, s, st);
         if (rc != DUGKS_OK) return rc;
+        nsteps += s;
         void* tmp = const_cast<void*>(cur);
         cur = nxt;
         nxt = tmp;
@@ -277,6 +340,11 @@ static int launch_run(dugks_batch* b, const void* f_in, void* f_out, const void*
     hipLaunchKernelGGL(k_batch_clock, dim3(1), dim3(1), 0, st, b->step_dev, (long long)nsteps, 0);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? DUGKS_OK : bfail(b, DUGKS_EHIP, hipGetErrorString(e));
+}
+
+static int launch_run(dugks_batch* b, const void* f_in, void* f_out, const void* forces, int nsteps, hipStream_t st)
+{
+    return launch_plan(b, f_in, f_out, forces, tile_plan(nsteps, b->D == 2 ? b->most : 1), st);
 }
 
 // per-instance force offsets into the instance table (before any launch)
@@ -372,28 +440,50 @@ extern "C" int dugks_batch_tune(dugks_batch* b, void* f_a, void* f_b, const void
     }
     float best = -1.0f;
     int best_tile = 0, best_chunk = 0, rc = DUGKS_OK;
-    // 0: a chunk per instance from the chunk model; else one chunk for all
-    static const int chunks[] = {0, 4, 8, 16, 32, 64};
-    for (int tile = 0; tile < fused_tile_variants(b->lattice) && rc == DUGKS_OK; ++tile) {
+    // time per step of nsteps launches of `steps` steps after a warm-up one
+    auto timed = [&](int steps, float& ms) {
+        const std::vector<int> warm(1, steps), plan(nsteps, steps);
+        int r = launch_plan(b, f_a, f_b, forces, warm, st);
+        if (r == DUGKS_OK && hipEventRecord(e0, st) != hipSuccess) r = bfail(b, DUGKS_EHIP, "event record");
+        if (r == DUGKS_OK) r = launch_plan(b, f_a, f_b, forces, plan, st);
+        if (r == DUGKS_OK && hipEventRecord(e1, st) != hipSuccess) r = bfail(b, DUGKS_EHIP, "event record");
+        if (r == DUGKS_OK && (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
+            r = bfail(b, DUGKS_EHIP, "event timing");
+        ms /= (float)steps;
+        return r;
+    };
+    if (b->D == 2) {
+        // 0: the model's steps per launch; 1: one fewer; 2: one more
+        int best_steps = b->model;
+        for (int tile = 0; tile < 3 && rc == DUGKS_OK; ++tile) {
+            const int steps = b->model + (tile == 1 ? -1 : tile == 2 ? 1 : 0);
+            if (steps < 1 || steps > TILE_MAX_STEPS || b->tblocks[steps] > (1LL << 26)) continue;
+            float ms = 0.0f;
+            rc = set_tiles(b, steps);
+            if (rc == DUGKS_OK) rc = timed(steps, ms);
+            if (rc == DUGKS_OK && (best < 0.0f || ms < best)) { best = ms; best_tile = tile; best_steps = steps; }
+        }
+        if (rc == DUGKS_OK) rc = set_most(b, best_steps);
+        drop_graph(b);
+    } else {
+        // 0: a chunk per instance from the chunk model; else one chunk for all
+        static const int chunks[] = {0, 4, 8, 16, 32, 64};
         for (int chunk : chunks) {
             if (chunk > 2 * maxm) continue;
-            rc = set_geometry(b, tile, chunk);
-            if (rc == DUGKS_OK) rc = launch_run(b, f_a, f_b, forces, 1, st);  // warm-up
-            if (rc == DUGKS_OK && hipEventRecord(e0, st) != hipSuccess) rc = bfail(b, DUGKS_EHIP, "event record");
-            if (rc == DUGKS_OK) rc = launch_run(b, f_a, f_b, forces, nsteps, st);
-            if (rc == DUGKS_OK && hipEventRecord(e1, st) != hipSuccess) rc = bfail(b, DUGKS_EHIP, "event record");
             float ms = 0.0f;
-            if (rc == DUGKS_OK && (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
-                rc = bfail(b, DUGKS_EHIP, "event timing");
+            rc = set_geometry(b, chunk);
+            if (rc == DUGKS_OK) rc = timed(1, ms);
             if (rc != DUGKS_OK) break;
-            if (best < 0.0f || ms < best) { best = ms; best_tile = tile; best_chunk = chunk; }
+            if (best < 0.0f || ms < best) { best = ms; best_chunk = chunk; }
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != DUGKS_OK) return rc;
-    rc = set_geometry(b, best_tile, best_chunk);
-    if (rc != DUGKS_OK) return rc;
+    if (b->D == 3) {
+        rc = set_geometry(b, best_chunk);
+        if (rc != DUGKS_OK) return rc;
+    }
     hipLaunchKernelGGL(k_batch_clock, dim3(1), dim3(1), 0, st, b->step_dev, clock, 1);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return bfail(b, DUGKS_EHIP, hipGetErrorString(e));
@@ -413,6 +503,8 @@ extern "C" void dugks_batch_destroy(dugks_batch* b)
     if (b->cstart_dev) (void)hipFree(b->cstart_dev);
     if (b->geom_dev) (void)hipFree(b->geom_dev);
     if (b->step_dev) (void)hipFree(b->step_dev);
+    for (TileBlock* t : b->tiles_dev)
+        if (t) (void)hipFree(t);
     delete b;
 }
 

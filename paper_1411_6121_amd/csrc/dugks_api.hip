@@ -254,6 +254,7 @@ void fill_inst(const dugks_config* c, Inst<T>& P, T* met_dev, std::vector<T>& me
     }
     P.omega = c->omega;
     P.phase = c->phase;
+    P.gphase = std::cos(c->phase);
     P.dtd = c->dt;
     met_host.clear();
     for (int a = 0; a < D; ++a) {
@@ -667,11 +668,22 @@ extern "C" int dugks_step(dugks_ctx* ctx, const void* f_in, void* f_out, const v
     return DUGKS_DISPATCH(ctx, step_dispatch, f_in, f_out, force, t_n, (hipStream_t)stream);
 }
 
+namespace dugks {
+int resolve_step_kernel(const dugks_ctx* ctx, bool field);
+int tile_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0, int nsteps, hipStream_t st,
+             int* which_out);
+}  // namespace dugks
+
 extern "C" int dugks_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0, int nsteps,
                          void* stream, int* which_out)
 {
     if (!ctx) return fail(nullptr, DUGKS_EINVAL, "null context");
     if (nsteps < 0) return fail(ctx, DUGKS_EINVAL, "negative step count");
+    // D2Q9 on its default kernel: several steps per launch (a single step, and
+    // every error case, as dugks_step has them)
+    if (nsteps > 1 && ctx->cfg.lattice == DUGKS_D2Q9 && f_a && f_b && f_a != f_b && std::isfinite(t0) &&
+        std::isfinite(t0 + (nsteps - 1) * ctx->cfg.dt) && dugks::resolve_step_kernel(ctx, force != nullptr) == 3)
+        return dugks::tile_run(ctx, f_a, f_b, force, t0, nsteps, (hipStream_t)stream, which_out);
     void* cur = f_a;
     void* nxt = f_b;
     int which = 0;
@@ -737,9 +749,6 @@ extern "C" int dugks_velocity_change(dugks_ctx* ctx, const void* f_a, const void
     return DUGKS_OK;
 }
 
-namespace dugks {
-int resolve_step_kernel(const dugks_ctx* ctx, bool field);
-}
 extern "C" int dugks_kernel_variant(const dugks_ctx* ctx) { return ctx ? dugks::resolve_step_kernel(ctx, false) : -1; }
 
 extern "C" void dugks_destroy(dugks_ctx* ctx)

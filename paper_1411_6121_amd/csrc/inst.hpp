@@ -78,6 +78,7 @@ struct Inst {
     T rhowo[6];    // oscillating part of the wall density: p_w,osc / RT
     T rlo[3], rhi[3]; // ghost(-1) = (1-rlo) phi(0) + rlo phi(1); ghost(n) likewise
     double omega, phase;
+    double gphase; // cos(phase): the time factor of a constant acceleration (omega = 0)
     double dtd;    // dt in double (time stamps of the time factor)
     AxisMetric<T> m[3];
 };
@@ -90,6 +91,7 @@ struct BatchGeom {
 template <typename T>
 __host__ __device__ inline T tfac(const Inst<T>& P, double t)
 {
+    if (P.omega == 0.0) return (T)P.gphase;
     return (T)cos(P.omega * t + P.phase);
 }
 

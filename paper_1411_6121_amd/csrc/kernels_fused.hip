@@ -626,6 +626,8 @@ int default_step_kernel(int lattice, int dtype, bool uniform, bool field)
 }
 
 int split_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t, hipStream_t st, int chunk);
+int tile_steps(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t0, long long k0, int steps,
+               hipStream_t st);
 
 int setup_fast(dugks_ctx* ctx)
 {
@@ -653,7 +655,9 @@ int resolve_step_kernel(const dugks_ctx* ctx, bool field)
     // incompressible choice and no force field is given, else the general
     // kernels
     if (ctx->cfg.model != DUGKS_MODEL_INCOMPRESSIBLE) {
-        if (field || ctx->fast == 0) return 0;
+        if (ctx->fast == 0) return 0;
+        if (ctx->cfg.lattice == DUGKS_D2Q9) return ctx->fast == 4 || ctx->fast == 3 ? 3 : 0;
+        if (field) return 0;
         if (ctx->cfg.lattice == DUGKS_D3Q27) return 3;
         const bool uni = ctx->cfg.dtype == DUGKS_F64 ? ctx->pd.uni != 0 : ctx->pf.uni != 0;
         const int v = ctx->fast != 4 ? ctx->fast : default_step_kernel(ctx->cfg.lattice, ctx->cfg.dtype, uni, false);
@@ -675,6 +679,7 @@ int fast_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, do
     // tiles: D3Q19 18 x 14 columns (16 x 12 interior), D2Q9 rows of 128
     // columns (126 interior)
     const int chunk = ctx->chunk;  // 0: chosen per launch (auto_chunk)
+    if (variant == 3 && ctx->cfg.lattice == DUGKS_D2Q9) return tile_steps(ctx, fin, fout, force, t, 0, 1, st);
     if (variant == 3) return split_step(ctx, fin, fout, force, t, st, chunk);
     if (variant == 2) {
         if (ctx->cfg.lattice == DUGKS_D3Q19) {
@@ -694,22 +699,13 @@ int fast_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, do
 
 void release_fast(dugks_ctx*) {}
 
-// Tile shapes of the batched kernel: (columns along x, along y) incl. halo.
-// D3Q19 has one (18 x 14: the FP64 LDS ring fills a CU); D2Q9 rows of 128
-// (default), 64 or 256 columns, chosen per batch by the autotuner.
-int fused_tile_variants(int lattice) { return lattice == DUGKS_D3Q19 ? 1 : 3; }
-
-void fused_tile_shape(int lattice, int variant, int* bx, int* by)
+// Tile of the batched D3Q19 kernels: columns along x and y incl. halo (18 x
+// 14: the FP64 LDS ring fills a CU)
+void fused_tile_shape(int* bx, int* by)
 {
-    if (lattice == DUGKS_D3Q19) {
-        *bx = 18;
-        *by = 14;
-        return;
-    }
-    *bx = variant == 1 ? 64 : (variant == 2 ? 256 : 128);
-    *by = 1;
+    *bx = 18;
+    *by = 14;
 }
-
 
 template <class LAT, typename T, int BX, int BY, int MINW, bool PF, bool FF>
 static hipError_t fused2_batch_ff(const void* insts, const long long* bstart, const BatchGeom* geom, int n,
@@ -743,11 +739,11 @@ static hipError_t fused2_batch_t(const void* insts, const long long* bstart, con
                                                             step, st);
 }
 
-hipError_t split_batch_launch(int lattice, int dtype, int variant, const void* insts, const long long* bstart,
-                              const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
-                              void* fout, const long long* step0, int step, hipStream_t st);
+hipError_t split_batch_launch(int dtype, const void* insts, const long long* bstart, const BatchGeom* geom, int n,
+                              long long nblocks, const void* fin, const void* forces, void* fout,
+                              const long long* step0, int step, hipStream_t st);
 
-long long split_batch_slots(int lattice, int dtype, int variant, int n_cu);
+long long split_batch_slots(int dtype, int n_cu);
 
 template <class LAT, typename T, int BX, int BY, int MINW>
 static long long fused2_batch_slots_t(int n_cu)
@@ -756,48 +752,26 @@ static long long fused2_batch_slots_t(int n_cu)
     return resident_slots(k_fused2_batch<LAT, T, BX, BY, MINW, PF, false>, BX * BY, fused2_lds<LAT, T, BX, BY>(), n_cu);
 }
 
-// workgroups of the batched step kernel (the one batch_step_launch takes)
-// resident on the device at once
-long long batch_resident_slots(int lattice, int dtype, bool uniform, int variant, int n_cu)
+// workgroups of the batched D3Q19 step kernel (the one batch_step_launch
+// takes) resident on the device at once
+long long batch_resident_slots(int dtype, bool uniform, int n_cu)
 {
-    if (default_step_kernel(lattice, dtype, uniform, false) == 3) return split_batch_slots(lattice, dtype, variant, n_cu);
-    if (lattice == DUGKS_D2Q9) {
-        if (dtype == DUGKS_F64) {
-            if (variant == 1) return fused2_batch_slots_t<D2Q9, double, 64, 1, 2>(n_cu);
-            if (variant == 2) return fused2_batch_slots_t<D2Q9, double, 256, 1, 2>(n_cu);
-            return fused2_batch_slots_t<D2Q9, double, 128, 1, 2>(n_cu);
-        }
-        if (variant == 1) return fused2_batch_slots_t<D2Q9, float, 64, 1, 2>(n_cu);
-        if (variant == 2) return fused2_batch_slots_t<D2Q9, float, 256, 1, 2>(n_cu);
-        return fused2_batch_slots_t<D2Q9, float, 128, 1, 2>(n_cu);
-    }
+    if (default_step_kernel(DUGKS_D3Q19, dtype, uniform, false) == 3) return split_batch_slots(dtype, n_cu);
     return dtype == DUGKS_F64 ? fused2_batch_slots_t<D3Q19, double, 18, 14, 1>(n_cu)
                               : fused2_batch_slots_t<D3Q19, float, 18, 14, 2>(n_cu);
 }
 
-// one batched step on the default step kernel of the lattice and precision
-// (so that batched and single-instance runs give identical states)
-hipError_t batch_step_launch(int lattice, int dtype, bool uniform, int variant, const void* insts,
-                             const long long* bstart, const BatchGeom* geom, int n, long long nblocks, const void* fin,
-                             const void* forces, void* fout, const long long* step0, int step, hipStream_t st)
+// one batched D3Q19 step on the default step kernel of the precision (so that
+// batched and single-instance runs take the same kernel)
+hipError_t batch_step_launch(int dtype, bool uniform, const void* insts, const long long* bstart,
+                             const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
+                             void* fout, const long long* step0, int step, hipStream_t st)
 {
-    if (default_step_kernel(lattice, dtype, uniform, forces != nullptr) == 3)
-        return split_batch_launch(lattice, dtype, variant, insts, bstart, geom, n, nblocks, fin, forces, fout, step0,
-                                  step, st);
-#define DUGKS_BATCH_ARGS insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st
-    if (lattice == DUGKS_D2Q9) {
-        if (dtype == DUGKS_F64) {
-            if (variant == 1) return fused2_batch_t<D2Q9, double, 64, 1, 2>(DUGKS_BATCH_ARGS);
-            if (variant == 2) return fused2_batch_t<D2Q9, double, 256, 1, 2>(DUGKS_BATCH_ARGS);
-            return fused2_batch_t<D2Q9, double, 128, 1, 2>(DUGKS_BATCH_ARGS);
-        }
-        if (variant == 1) return fused2_batch_t<D2Q9, float, 64, 1, 2>(DUGKS_BATCH_ARGS);
-        if (variant == 2) return fused2_batch_t<D2Q9, float, 256, 1, 2>(DUGKS_BATCH_ARGS);
-        return fused2_batch_t<D2Q9, float, 128, 1, 2>(DUGKS_BATCH_ARGS);
-    }
-    return dtype == DUGKS_F64 ? fused2_batch_t<D3Q19, double, 18, 14, 1>(DUGKS_BATCH_ARGS)
-                              : fused2_batch_t<D3Q19, float, 18, 14, 2>(DUGKS_BATCH_ARGS);
-#undef DUGKS_BATCH_ARGS
+    if (default_step_kernel(DUGKS_D3Q19, dtype, uniform, forces != nullptr) == 3)
+        return split_batch_launch(dtype, insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st);
+    if (dtype == DUGKS_F64)
+        return fused2_batch_t<D3Q19, double, 18, 14, 1>(insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st);
+    return fused2_batch_t<D3Q19, float, 18, 14, 2>(insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st);
 }
 
 }  // namespace dugks

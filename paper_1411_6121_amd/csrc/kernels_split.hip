@@ -1177,9 +1177,7 @@ int split_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, d
             return launch_split<D3Q19, double, 16, 8, 2, false>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
         return launch_split<D3Q19, float, 18, 14, 2, false>(ctx, ctx->pf, fin, fout, force, t, st, chunk);
     }
-    if (ctx->cfg.dtype == DUGKS_F64)
-        return launch_split<D2Q9, double, 128, 1, 2, false>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
-    return launch_split<D2Q9, float, 128, 1, 2, false>(ctx, ctx->pf, fin, fout, force, t, st, chunk);
+    return fail(ctx, DUGKS_EUNSUPPORTED, "no two-lane kernel of this lattice");
 }
 
 template <class LAT, typename T, int BX, int BY, int MINW, bool PF, bool FF>
@@ -1221,40 +1219,21 @@ static long long split_batch_slots_t(int n_cu)
 }
 
 // workgroups of the batched two-lane kernel resident on the device at once
-long long split_batch_slots(int lattice, int dtype, int variant, int n_cu)
+long long split_batch_slots(int dtype, int n_cu)
 {
-    if (lattice == DUGKS_D2Q9) {
-        if (dtype == DUGKS_F64) {
-            if (variant == 1) return split_batch_slots_t<D2Q9, double, 64, 1, 2, false>(n_cu);
-            if (variant == 2) return split_batch_slots_t<D2Q9, double, 256, 1, 2, false>(n_cu);
-            return split_batch_slots_t<D2Q9, double, 128, 1, 2, false>(n_cu);
-        }
-        if (variant == 1) return split_batch_slots_t<D2Q9, float, 64, 1, 2, false>(n_cu);
-        if (variant == 2) return split_batch_slots_t<D2Q9, float, 256, 1, 2, false>(n_cu);
-        return split_batch_slots_t<D2Q9, float, 128, 1, 2, false>(n_cu);
-    }
     return dtype == DUGKS_F64 ? split_batch_slots_t<D3Q19, double, 18, 14, 1, false>(n_cu)
                               : split_batch_slots_t<D3Q19, float, 18, 14, 2, false>(n_cu);
 }
 
-hipError_t split_batch_launch(int lattice, int dtype, int variant, const void* insts, const long long* bstart,
-                              const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
-                              void* fout, const long long* step0, int step, hipStream_t st)
+hipError_t split_batch_launch(int dtype, const void* insts, const long long* bstart, const BatchGeom* geom, int n,
+                              long long nblocks, const void* fin, const void* forces, void* fout,
+                              const long long* step0, int step, hipStream_t st)
 {
-#define DUGKS_SPLIT_ARGS insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st
-    if (lattice == DUGKS_D2Q9) {
-        if (dtype == DUGKS_F64) {
-            if (variant == 1) return split_batch_launch_t<D2Q9, double, 64, 1, 2, false>(DUGKS_SPLIT_ARGS);
-            if (variant == 2) return split_batch_launch_t<D2Q9, double, 256, 1, 2, false>(DUGKS_SPLIT_ARGS);
-            return split_batch_launch_t<D2Q9, double, 128, 1, 2, false>(DUGKS_SPLIT_ARGS);
-        }
-        if (variant == 1) return split_batch_launch_t<D2Q9, float, 64, 1, 2, false>(DUGKS_SPLIT_ARGS);
-        if (variant == 2) return split_batch_launch_t<D2Q9, float, 256, 1, 2, false>(DUGKS_SPLIT_ARGS);
-        return split_batch_launch_t<D2Q9, float, 128, 1, 2, false>(DUGKS_SPLIT_ARGS);
-    }
-    return dtype == DUGKS_F64 ? split_batch_launch_t<D3Q19, double, 18, 14, 1, false>(DUGKS_SPLIT_ARGS)
-                              : split_batch_launch_t<D3Q19, float, 18, 14, 2, false>(DUGKS_SPLIT_ARGS);
-#undef DUGKS_SPLIT_ARGS
+    if (dtype == DUGKS_F64)
+        return split_batch_launch_t<D3Q19, double, 18, 14, 1, false>(insts, bstart, geom, n, nblocks, fin, forces, fout,
+                                                                     step0, step, st);
+    return split_batch_launch_t<D3Q19, float, 18, 14, 2, false>(insts, bstart, geom, n, nblocks, fin, forces, fout,
+                                                                step0, step, st);
 }
 
 }  // namespace dugks

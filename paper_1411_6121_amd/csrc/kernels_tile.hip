@@ -1,0 +1,585 @@
+// kernels_tile.hip -- the D2Q9 step on tiles of 32 x 16 cells, one lane per
+// cell, several time steps per launch.
+//
+// A workgroup loads a tile of the state into registers and advances it S
+// steps; cells within S of the tile's edge lose their neighbours one layer
+// per step, so neighbouring tiles overlap by 2 S and the 32 - 2 S by 16 - 2 S
+// cells inside are written.  Along x a lane's neighbours are the lanes beside
+// it (DPP wave shifts; a wave holds two rows of 32); along y they are
+// exchanged through LDS.  With
+//   psi_y(c) = f-bar-plus(c) - h xi_x d_x f-bar-plus(c)   (psi_x likewise)
+// formed once per cell, an interface value is (1 - w) psi_L + w psi_R - h
+// xi_n (f-bar-plus_R - f-bar-plus_L) / (x_R - x_L) (Eq. gradient), and every
+// interface of a tile is evaluated once: a lane takes its cell's upper x and
+// upper y interface.  The LDS holds 13 values per cell for the row above and
+// below and the 6 fluxes of the upper y interface: 76 KB in FP64, two
+// workgroups per CU.
+//
+// What bounds it: FP64 issue (about 570 instructions per wave and step, 8
+// waves a tile) on meshes that fill the chip, the latency of one tile's chain
+// on small ones; the state crosses memory once per launch.  us a step, against
+// the kernel that marches rows of 128 columns with two lanes per column, one
+// step per launch: 1024^2 cavity FP64 28.7 against 52.7 and FP32 18 against
+// 37, 128^2 stretched cavity FP64 3.5 against 8.95, 40 x 20 channel FP64 3.8
+// against 8.9, 64 uneven instances FP64 126 against 175.  A march along y with
+// the rows in registers and no LDS (one lane per column, one step per launch)
+// took 41, 26, 8.5 and 8.3.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <utility>
+#include <vector>
+
+#include "ctx.hpp"
+#include "kernels_general.hpp"
+#include "march.hpp"
+#include "wave.hpp"
+
+namespace dugks {
+
+constexpr int TILE_X = 32, TILE_Y = 16, TILE_NT = TILE_X * TILE_Y;
+constexpr int TILE_SLOTS = 19;
+static_assert(2 * TILE_MAX_STEPS < TILE_Y, "a tile needs rows of its own");
+
+// LDS slots of a cell: f-bar-plus of the velocities with e_y != 0 in 0..5,
+// psi_y of those with e_x != 0 in 6..11, the rest velocity in 12, the upper y
+// interface's original values in 13..18
+__host__ __device__ constexpr int slot_phi(int q) { return q == 0 ? 0 : q == 2 ? 1 : q == 3 ? 2 : q == 5 ? 3 : q == 6 ? 4 : 5; }
+__host__ __device__ constexpr int slot_psi(int q)
+{
+    return q == 4 ? 12 : (q == 3 || q == 5) ? slot_phi(q) : 6 + (q < 3 ? q : q - 3);
+}
+
+// coefficients of one cell along one axis: its upper interface's weight and
+// h c / (x_R - x_L), h c times its derivative coefficients, c dt / Delta
+template <typename T>
+struct AxisCoef {
+    T w, k, kp, km, fd;
+};
+
+template <typename T, bool UNI>
+__device__ __forceinline__ AxisCoef<T> axis_coef(const Inst<T>& P, int a, int j, int f)
+{
+    const T hc = P.h * P.c;
+    if constexpr (UNI) return AxisCoef<T>{T(0.5), hc * P.ugn[a], T(2) * (hc * P.uct[a]), T(0), P.ufdx[a] * P.c};
+    const AxisMetric<T>& m = P.m[a];
+    return AxisCoef<T>{m.w[f], hc * m.gn[f], hc * m.cp[j], hc * m.cm[j], m.fdx[j] * P.c};
+}
+
+// cell of coordinate i on a periodic axis of n cells (-TILE_X < i < n + TILE_X)
+__device__ __forceinline__ int tile_wrap(int i, int n)
+{
+    if (n >= TILE_X) return i < 0 ? i + n : (i >= n ? i - n : i);
+    return ((i % n) + n) % n;
+}
+
+// One workgroup's work: tile (tx, ty) of instance P, `steps` steps from time
+// index k0 (time t0 + k dt).  ACC: there is an acceleration; FIELD: part of it
+// is a force field (force may still be null: a batch where only some
+// instances have one).
+// NW: no cell of the tile lies at or beyond a wall.  REREAD: the y stage reads
+// the cell's own values back from LDS instead of holding them in registers
+// over the x stage (the wall body at four waves per SIMD).
+template <typename T, bool UNI, bool ACC, bool FIELD, bool ORIG, bool NW, bool REREAD>
+__device__ __forceinline__ void tile_body(const Inst<T>& P, const T* __restrict__ fin, const T* __restrict__ force,
+                                          T* __restrict__ fout, double t0, long long k0, int steps, int btx, int bty,
+                                          T* lds)
+{
+#pragma clang fp contract(off)
+    const int tid = (int)threadIdx.x;
+    const int cx = tid & (TILE_X - 1), r = tid / TILE_X;
+    const int nx = P.n[0], ny = P.n[1];
+    const long long nc = P.nc;
+    const bool perx = P.per[0] != 0, pery = P.per[1] != 0;
+    const int gx = btx * (TILE_X - 2 * steps) - steps + cx, gy = bty * (TILE_Y - 2 * steps) - steps + r;
+    // source cell: wrapped on a periodic axis; beyond a wall the nearest cell
+    // (ghost columns are overwritten, what lies further is never used)
+    const int sx = perx ? tile_wrap(gx, nx) : min(max(gx, 0), nx - 1);
+    const int sy = pery ? tile_wrap(gy, ny) : min(max(gy, 0), ny - 1);
+    const bool own = cx >= steps && cx < TILE_X - steps && r >= steps && r < TILE_Y - steps && gx < nx && gy < ny;
+    const bool glo = !NW && !perx && gx == -1, ghi = !NW && !perx && gx == nx;
+    const bool bot = !NW && !pery && gy == 0, top = !NW && !pery && gy == ny - 1;
+    // the tile holds a ghost column of the low / high x wall (workgroup-uniform)
+    const bool xlo = !NW && !perx && btx * (TILE_X - 2 * steps) - steps < 0;
+    const bool xhi = !NW && !perx && btx * (TILE_X - 2 * steps) - steps + TILE_X > nx;
+    const long long ci = (long long)sy * nx + sx;
+    T f[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) f[q] = fin[q * nc + ci];
+    const int fx_i = min(max(gx + 1, 0), nx);
+    const AxisCoef<T> mx = axis_coef<T, UNI>(P, 0, sx, perx ? sx + 1 : fx_i);
+    const AxisCoef<T> my = axis_coef<T, UNI>(P, 1, sy, sy + 1);
+    const T rxl = P.rlo[0], rxh = P.rhi[0], ryl = P.rlo[1], ryh = P.rhi[1];
+    // the force field of the cell and, interpolated, of its upper interfaces
+    // (and of a wall row's lower one): constant over the steps
+    T g0 = T(0), g1 = T(0), gyu[2] = {T(0), T(0)}, gyl[2] = {T(0), T(0)}, gxu[2] = {T(0), T(0)};
+    T wyl = T(0.5), kyl = my.k;  // lower y interface of a wall row
+    if constexpr (!UNI) {
+        wyl = P.m[1].w[sy];
+        kyl = P.h * P.c * P.m[1].gn[sy];
+    }
+    if constexpr (FIELD) {
+        if (force) {
+            const int up = top ? max(sy - 1, 0) : (pery && sy == ny - 1 ? 0 : min(sy + 1, ny - 1));
+            const int dn = pery && sy == 0 ? ny - 1 : max(sy - 1, 0);
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                const T* fd = force + d * nc;
+                T own_v = fd[ci], up_v = fd[(long long)up * nx + sx], dn_v = fd[(long long)dn * nx + sx];
+                if (xlo) {
+                    const T a1 = lane_next(own_v), b1 = lane_next(up_v), c1 = lane_next(dn_v);
+                    const T a2 = lane_next(a1), b2 = lane_next(b1), c2 = lane_next(c1);
+                    if (glo) {
+                        own_v = fma_(rxl, a2 - a1, a1);
+                        up_v = fma_(rxl, b2 - b1, b1);
+                        dn_v = fma_(rxl, c2 - c1, c1);
+                    }
+                }
+                if (xhi) {
+                    const T a1 = lane_prev(own_v), b1 = lane_prev(up_v), c1 = lane_prev(dn_v);
+                    const T a2 = lane_prev(a1), b2 = lane_prev(b1), c2 = lane_prev(c1);
+                    if (ghi) {
+                        own_v = fma_(rxh, a2 - a1, a1);
+                        up_v = fma_(rxh, b2 - b1, b1);
+                        dn_v = fma_(rxh, c2 - c1, c1);
+                    }
+                }
+                if (d == 0) g0 = own_v;
+                else g1 = own_v;
+                const T ab = top ? fma_(ryh, up_v - own_v, own_v) : up_v;
+                const T be = bot ? fma_(ryl, up_v - own_v, own_v) : dn_v;
+                gyu[d] = fma_(my.w, ab - own_v, own_v);
+                gyl[d] = fma_(wyl, own_v - be, be);
+                const T rt = lane_next(own_v);
+                gxu[d] = fma_(mx.w, rt - own_v, own_v);
+            }
+        }
+    }
+    // the time factors of the steps: lane 2 s takes step s's, lane 2 s + 1
+    // that of its interface time
+    T tf = (T)P.gphase;
+    if (P.omega != 0.0) {
+        const int l = tid & 63, s = l >> 1;
+        const double t = t0 + (double)(k0 + s) * P.dtd;
+        tf = tfac(P, (l & 1) ? t + 0.5 * P.dtd : t);
+    }
+    auto ghost1 = [&](T& a) {
+        if (xlo) {
+            const T s1 = lane_next(a), s2 = lane_next(s1);
+            if (glo) a = fma_(rxl, s2 - s1, s1);
+        }
+        if (xhi) {
+            const T s1 = lane_prev(a), s2 = lane_prev(s1);
+            if (ghi) a = fma_(rxh, s2 - s1, s1);
+        }
+    };
+    auto at = [&](int slot, int row) -> T& { return lds[slot * TILE_NT + row * TILE_X + cx]; };
+    const int ru = min(r + 1, TILE_Y - 1), rd = max(r - 1, 0);
+    const T hh = T(0.5) * P.h;
+
+    for (int s = 0; s < steps; ++s) {
+        const T gt = P.omega != 0.0 ? __shfl(tf, 2 * s) : tf, gth = P.omega != 0.0 ? __shfl(tf, 2 * s + 1) : tf;
+        T phi[9], ps[9];
+        {
+            T Gx = T(0), Gy = T(0);
+            if constexpr (ACC) {
+                Gx = gt * (P.G0[0] + g0);
+                Gy = gt * (P.G0[1] + g1);
+            }
+            d2_phi<T, ORIG, ACC>(P, f, Gx, Gy, phi);
+        }
+        if (xlo || xhi) {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) ghost1(phi[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            const int e = D2Q9::ex(q);
+            ps[q] = e == 0 ? phi[q] : d2_psi<T, UNI>(e, mx.kp, mx.km, lane_prev(phi[q]), phi[q], lane_next(phi[q]));
+            if (D2Q9::ey(q) != 0) at(slot_phi(q), r) = phi[q];
+            if (e != 0 || q == 4) at(slot_psi(q), r) = ps[q];
+        }
+        // f~+ of Eq. (f_tilde_+); the fluxes are added as they come
+#pragma unroll
+        for (int q = 0; q < 9; ++q) f[q] = fma_(phi[q] - f[q], T(1.0 / 3.0), phi[q]);
+        __syncthreads();
+        // the upper x interface; the lower one is that of the lane before
+        {
+            T v[9];
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                const int e = D2Q9::ey(q);
+                T p = phi[q];
+                if (e != 0) {
+                    // the ghost row beyond a wall by extrapolation
+                    T u = at(slot_phi(q), ru), d = at(slot_phi(q), rd);
+                    if constexpr (!NW) {
+                        const T gu = fma_(ryh, d - p, p), gd = fma_(ryl, u - p, p);
+                        u = top ? gu : u;
+                        d = bot ? gd : d;
+                    }
+                    p = d2_psi<T, UNI>(e, my.kp, my.km, d, p, u);
+                }
+                const T pR = lane_next(p);
+                const T hR = (e != 0 && D2Q9::ex(q) != 0) ? lane_next(phi[q]) : pR;
+                v[q] = d2_recon<T, UNI>(D2Q9::ex(q), mx.w, mx.k, p, pR, phi[q], hR);
+            }
+            const T Gx = ACC ? gth * (P.G0[0] + gxu[0]) : T(0), Gy = ACC ? gth * (P.G0[1] + gxu[1]) : T(0);
+            T rho;
+            EqD2<T> E = d2_point<T, ORIG, ACC>(P, v, Gx, Gy, hh, rho);
+            if (xlo || xhi) {
+                // wall faces: the opposite interface is the upper face of the
+                // next lane (low wall, ghost lane) or of the previous one
+                if (xlo) {
+                    NeqD2<T> I;
+                    d2_capture<T, 0>(E, rho, v, 1, I);
+                    I.rho = lane_next(I.rho);
+                    I.ux = lane_next(I.ux);
+                    I.uy = lane_next(I.uy);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) I.ne[k] = lane_next(I.ne[k]);
+                    if (glo) d2_wall<T, 0, ORIG>(P, 0, 1, v, I, gth);
+                }
+                if (xhi) {
+                    NeqD2<T> I;
+                    d2_capture<T, 0>(E, rho, v, -1, I);
+                    I.rho = lane_prev(I.rho);
+                    I.ux = lane_prev(I.ux);
+                    I.uy = lane_prev(I.uy);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) I.ne[k] = lane_prev(I.ne[k]);
+                    if (gx == nx - 1) d2_wall<T, 0, ORIG>(P, 1, -1, v, I, gth);
+                }
+                E = d2_point<T, ORIG, ACC>(P, v, Gx, Gy, hh, rho);
+            }
+            d2_relax_pair<T, ACC>(E, 6, P.B7, P.C7, v[6], v[2]);
+            d2_relax_pair<T, ACC>(E, 7, P.B7, P.C7, v[7], v[1]);
+            d2_relax_pair<T, ACC>(E, 8, P.B7, P.C7, v[8], v[0]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                f[k] = fma_(mx.fd, v[k] - lane_prev(v[k]), f[k]);
+                f[6 + k] = fma_(-mx.fd, v[6 + k] - lane_prev(v[6 + k]), f[6 + k]);
+            }
+        }
+        asm volatile("" ::: "memory");  // the y stage's LDS reads are not hoisted into the x stage
+        T vy[6];                        // the upper y interface
+        {
+            if constexpr (REREAD) {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) {
+                    ps[q] = at(slot_psi(q), r);
+                    if (D2Q9::ey(q) != 0) phi[q] = at(slot_phi(q), r);
+                }
+            }
+            // the interface between this row and the row at LDS index rr
+            // (above: the upper interface; below: its mirror, the lower one)
+            auto face_values = [&](bool lower, T (&v)[9]) {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) {
+                    const int rr = lower ? rd : ru;
+                    const T pn = at(slot_psi(q), rr);
+                    const T hn = D2Q9::ey(q) == 0 ? T(0) : D2Q9::ex(q) == 0 ? pn : at(slot_phi(q), rr);
+                    if (lower) v[q] = d2_recon<T, UNI>(D2Q9::ey(q), wyl, kyl, pn, ps[q], hn, phi[q]);
+                    else v[q] = d2_recon<T, UNI>(D2Q9::ey(q), my.w, my.k, ps[q], pn, phi[q], hn);
+                }
+            };
+            // a wall face: the row beyond it by extrapolation through this
+            // row and the one inside
+            auto wall_values = [&](bool lower, T (&v)[9]) {
+                const T re = lower ? ryl : ryh;
+                const int rr = lower ? ru : rd;
+#pragma unroll
+                for (int q = 0; q < 9; ++q) {
+                    T pn = at(slot_psi(q), rr);
+                    T hn = D2Q9::ey(q) == 0 ? T(0) : D2Q9::ex(q) == 0 ? pn : at(slot_phi(q), rr);
+                    pn = fma_(re, pn - ps[q], ps[q]);
+                    if (D2Q9::ey(q) != 0) hn = fma_(re, hn - phi[q], phi[q]);
+                    if (lower) v[q] = d2_recon<T, UNI>(D2Q9::ey(q), wyl, kyl, pn, ps[q], hn, phi[q]);
+                    else v[q] = d2_recon<T, UNI>(D2Q9::ey(q), my.w, my.k, ps[q], pn, phi[q], hn);
+                }
+            };
+            const T Gu0 = ACC ? gth * (P.G0[0] + gyu[0]) : T(0), Gu1 = ACC ? gth * (P.G0[1] + gyu[1]) : T(0);
+            const T Gl0 = ACC ? gth * (P.G0[0] + gyl[0]) : T(0), Gl1 = ACC ? gth * (P.G0[1] + gyl[1]) : T(0);
+            T v[9], rho;
+            if (!top) {
+                face_values(false, v);
+            } else {
+                // high wall: its opposite interface is this row's lower one
+                NeqD2<T> info;
+                face_values(true, v);
+                const EqD2<T> O = d2_point<T, ORIG, ACC>(P, v, Gl0, Gl1, hh, rho);
+                d2_capture<T, 1>(O, rho, v, -1, info);
+                wall_values(false, v);
+                d2_wall<T, 1, ORIG>(P, 3, -1, v, info, gth);
+            }
+            const EqD2<T> E = d2_point<T, ORIG, ACC>(P, v, Gu0, Gu1, hh, rho);
+            NeqD2<T> info;
+            if (bot) d2_capture<T, 1>(E, rho, v, 1, info);
+            d2_relax_pair<T, ACC>(E, 5, P.B7, P.C7, v[5], v[3]);
+            d2_relax_pair<T, ACC>(E, 6, P.B7, P.C7, v[6], v[2]);
+            d2_relax_pair<T, ACC>(E, 8, P.B7, P.C7, v[8], v[0]);
+            // the row below a wall stores nothing: its slot holds the wall
+            // face
+            if (NW || pery || gy != -1) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    at(13 + k, r) = v[3 * k];
+                    at(16 + k, r) = v[3 * k + 2];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                vy[k] = v[3 * k];
+                vy[3 + k] = v[3 * k + 2];
+            }
+            if (bot) {
+                // low wall: the opposite interface was the upper one
+                wall_values(true, v);
+                d2_wall<T, 1, ORIG>(P, 2, 1, v, info, gth);
+                const EqD2<T> B = d2_point<T, ORIG, ACC>(P, v, Gl0, Gl1, hh, rho);
+                d2_relax_pair<T, ACC>(B, 5, P.B7, P.C7, v[5], v[3]);
+                d2_relax_pair<T, ACC>(B, 6, P.B7, P.C7, v[6], v[2]);
+                d2_relax_pair<T, ACC>(B, 8, P.B7, P.C7, v[8], v[0]);
+                if (r > 0) {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        at(13 + k, r - 1) = v[3 * k];
+                        at(16 + k, r - 1) = v[3 * k + 2];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            f[3 * k] = fma_(my.fd, vy[k] - at(13 + k, rd), f[3 * k]);
+            f[3 * k + 2] = fma_(-my.fd, vy[3 + k] - at(16 + k, rd), f[3 * k + 2]);
+        }
+    }
+    if (own) {
+        T* o = fout + ((long long)gy * nx + gx);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) o[q * nc] = f[q];
+    }
+}
+
+// does the tile, halo included, stay clear of every wall and its ghosts?
+template <typename T>
+__device__ __forceinline__ bool tile_no_wall(const Inst<T>& P, int steps, int btx, int bty)
+{
+    const int x0 = btx * (TILE_X - 2 * steps) - steps, y0 = bty * (TILE_Y - 2 * steps) - steps;
+    if (!P.per[0] && (x0 < 0 || x0 + TILE_X > P.n[0])) return false;
+    if (!P.per[1] && (y0 <= 0 || y0 + TILE_Y >= P.n[1])) return false;
+    return true;
+}
+
+// Waves per SIMD the kernel is compiled for.  Many tiles: four (two tiles per
+// CU; the body without wall code fits 128 registers, the wall body spills a
+// few).  At most one tile per CU (SMALL): two, since no more waves come; the
+// wall body then spills nothing (128^2 cavity FP64: 3.7 against 4.6 us a
+// step), and without the other body less code is fetched on a first pass.
+#define TILE_BOUNDS(W) __attribute__((amdgpu_flat_work_group_size(TILE_NT, TILE_NT), amdgpu_waves_per_eu(W)))
+
+template <typename T, bool UNI, bool ACC, bool FIELD, bool ORIG, bool SMALL>
+__global__ TILE_BOUNDS((SMALL ? 2 : 4)) void k_tile(const Inst<T>* __restrict__ Pp, const T* __restrict__ fin,
+                                                    const T* __restrict__ force, T* __restrict__ fout, double t0,
+                                                    long long k0, int steps, int tiles_x)
+{
+    __shared__ T lds[TILE_SLOTS * TILE_NT];
+    const int b = xcd_order((int)blockIdx.x, (int)gridDim.x);
+    const Inst<T>& P = *Pp;
+    const int bx = b % tiles_x, by = b / tiles_x;
+    if (!SMALL && tile_no_wall(P, steps, bx, by))
+        tile_body<T, UNI, ACC, FIELD, ORIG, true, false>(P, fin, force, fout, t0, k0, steps, bx, by, lds);
+    else
+        tile_body<T, UNI, ACC, FIELD, ORIG, false, !SMALL && sizeof(T) == 8>(P, fin, force, fout, t0, k0, steps, bx, by, lds);
+}
+
+// many instances in one launch: blocks[b] is the instance and the tile of
+// workgroup b in XCD order; instance i is at time index *step0 + step (a device
+// counter, so a captured graph replays with advancing time)
+template <typename T, bool FIELD>
+__global__ TILE_BOUNDS(4) void k_tile_batch(const Inst<T>* __restrict__ insts, const TileBlock* __restrict__ blocks,
+                                            const T* __restrict__ fin, const T* __restrict__ forces,
+                                            T* __restrict__ fout, const long long* __restrict__ step0, int step,
+                                            int steps)
+{
+    __shared__ T lds[TILE_SLOTS * TILE_NT];
+    const TileBlock k = blocks[xcd_order((int)blockIdx.x, (int)gridDim.x)];
+    const Inst<T>& P = insts[k.inst];
+    const int bx = k.bx, by = k.by;
+    const long long k0 = *step0 + step;
+    const T* force = (FIELD && forces && P.foff >= 0) ? forces + P.foff : nullptr;
+    const bool nw = tile_no_wall(P, steps, bx, by);
+    fin += P.off;
+    fout += P.off;
+    if (P.uni) {
+        if (nw) tile_body<T, true, true, FIELD, false, true, false>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+        else tile_body<T, true, true, FIELD, false, false, sizeof(T) == 8>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+    } else {
+        if (nw) tile_body<T, false, true, FIELD, false, true, false>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+        else tile_body<T, false, true, FIELD, false, false, sizeof(T) == 8>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+// tiles of a launch of `steps` steps on an nx x ny mesh
+long long tile_count(int nx, int ny, int steps)
+{
+    const int ox = TILE_X - 2 * steps, oy = TILE_Y - 2 * steps;
+    return (long long)((nx + ox - 1) / ox) * ((ny + oy - 1) / oy);
+}
+
+// Time of a launch of `steps` steps on `tiles` tiles, in microseconds.  A
+// launch costs a, a tile with its CU to itself l per step (latency), and a CU
+// with several tiles m + c per step for each.  Fitted on MI355X to 40x20 to
+// 1024^2 meshes and 1 to 6 steps a launch (FP64 1024^2: 32.6, 27.1 and 29.8
+// us a step for 1, 2 and 3 steps a launch; 128^2 cavity: 7.4, 4.8, 4.1, 3.8,
+// 3.7 and 3.7 us for 1 to 6).
+static double tile_launch_us(bool f64, long long tiles, int steps, int n_cu)
+{
+    const double a = f64 ? 4.5 : 3.0, l = f64 ? 2.9 : 2.4, m = f64 ? 1.5 : 0.86, c = f64 ? 1.25 : 0.92;
+    const double per_cu = (double)((tiles + n_cu - 1) / (n_cu > 0 ? n_cu : 1));
+    return a + std::max(l * steps, per_cu * (m + c * steps));
+}
+
+// Steps per launch that give the shortest time per step: more steps save
+// launches and passes over memory, but overlap the tiles more.  `tiles_of`:
+// tiles for a number of steps per launch.
+template <class F>
+static int best_steps(bool f64, int n_cu, F tiles_of)
+{
+    int best = 1;
+    double best_us = 1e300;
+    for (int s = 1; s <= TILE_MAX_STEPS; ++s) {
+        const double us = tile_launch_us(f64, tiles_of(s), s, n_cu) / s;
+        if (us < best_us) {
+            best_us = us;
+            best = s;
+        }
+    }
+    return best;
+}
+
+// Launches of a run of nsteps steps with at most `most` steps each, as steps
+// per launch.  The run ends in the buffer that steps of their own would end
+// in (as many launches as steps, modulo 2), with the state before the last
+// step in the other one: the last launch is one step.
+std::vector<int> tile_plan(int nsteps, int most)
+{
+    std::vector<int> plan;
+    if (nsteps < 1) return plan;
+    const int n = nsteps - 1;
+    int m = (n + most - 1) / most;
+    if ((m ^ n) & 1) ++m;  // m <= n: n itself has the right parity
+    for (int i = 0; i < m; ++i) plan.push_back((int)((long long)n * (i + 1) / m - (long long)n * i / m));
+    plan.push_back(1);
+    return plan;
+}
+
+template <typename T, bool UNI, bool ACC, bool FIELD, bool ORIG>
+static int launch_tile(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t0,
+                       long long k0, int steps, hipStream_t st)
+{
+    const long long nb = tile_count(P.n[0], P.n[1], steps);
+    if (nb > 0x7fffffffLL) return fail(ctx, DUGKS_EUNSUPPORTED, "mesh too large for one launch");
+    const int ox = TILE_X - 2 * steps, tiles_x = (P.n[0] + ox - 1) / ox;
+    auto kern = (nb <= ctx->n_cu && !(P.per[0] && P.per[1])) ? k_tile<T, UNI, ACC, FIELD, ORIG, true>
+                                                             : k_tile<T, UNI, ACC, FIELD, ORIG, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(TILE_NT), 0, st, (const Inst<T>*)ctx->inst_dev, (const T*)fin,
+                       (const T*)force, (T*)fout, t0, k0, steps, tiles_x);
+    return hip_check(ctx, hipGetLastError(), "step launch");
+}
+
+template <typename T, bool UNI, bool ORIG>
+static int launch_tile_acc(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t0,
+                           long long k0, int steps, hipStream_t st)
+{
+    if (force) return launch_tile<T, UNI, true, true, ORIG>(ctx, P, fin, fout, force, t0, k0, steps, st);
+    if (P.G0[0] != T(0) || P.G0[1] != T(0))
+        return launch_tile<T, UNI, true, false, ORIG>(ctx, P, fin, fout, force, t0, k0, steps, st);
+    return launch_tile<T, UNI, false, false, ORIG>(ctx, P, fin, fout, force, t0, k0, steps, st);
+}
+
+template <typename T>
+static int launch_tile_t(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t0,
+                         long long k0, int steps, hipStream_t st)
+{
+    if (P.orig)
+        return P.uni ? launch_tile_acc<T, true, true>(ctx, P, fin, fout, force, t0, k0, steps, st)
+                     : launch_tile_acc<T, false, true>(ctx, P, fin, fout, force, t0, k0, steps, st);
+    return P.uni ? launch_tile_acc<T, true, false>(ctx, P, fin, fout, force, t0, k0, steps, st)
+                 : launch_tile_acc<T, false, false>(ctx, P, fin, fout, force, t0, k0, steps, st);
+}
+
+// `steps` steps from time index k0 (time t0 + k0 dt), fin -> fout
+int tile_steps(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t0, long long k0, int steps,
+               hipStream_t st)
+{
+    if (ctx->cfg.dtype == DUGKS_F64) return launch_tile_t<double>(ctx, ctx->pd, fin, fout, force, t0, k0, steps, st);
+    return launch_tile_t<float>(ctx, ctx->pf, fin, fout, force, t0, k0, steps, st);
+}
+
+// nsteps steps from f_a, as dugks_run; *which_out as there
+int tile_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0, int nsteps, hipStream_t st,
+             int* which_out)
+{
+    const bool f64 = ctx->cfg.dtype == DUGKS_F64;
+    const int nx = ctx->cfg.n[0], ny = ctx->cfg.n[1];
+    const int most = best_steps(f64, ctx->n_cu, [&](int s) { return tile_count(nx, ny, s); });
+    void* cur = f_a;
+    void* nxt = f_b;
+    long long k = 0;
+    for (int s : tile_plan(nsteps, most)) {
+        const int rc = tile_steps(ctx, cur, nxt, force, t0, k, s, st);
+        if (rc != DUGKS_OK) return rc;
+        std::swap(cur, nxt);
+        k += s;
+    }
+    if (which_out) *which_out = nsteps & 1;
+    return DUGKS_OK;
+}
+
+// steps per launch of a batch of n instances of nx[i] x ny[i] cells
+int tile_batch_steps(int dtype, int n, const int* nx, const int* ny, int n_cu)
+{
+    return best_steps(dtype == DUGKS_F64, n_cu, [&](int s) {
+        long long t = 0;
+        for (int i = 0; i < n; ++i) t += tile_count(nx[i], ny[i], s);
+        return t;
+    });
+}
+
+template <typename T>
+static void tile_batch_t(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
+                         const void* forces, void* fout, const long long* step0, int step, int steps, hipStream_t st)
+{
+    auto kern = forces ? k_tile_batch<T, true> : k_tile_batch<T, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(TILE_NT), 0, st, (const Inst<T>*)insts, blocks,
+                       (const T*)fin, (const T*)forces, (T*)fout, step0, step, steps);
+}
+
+// `steps` steps of every instance; blocks: the nblocks workgroups of a launch of
+// `steps` steps
+hipError_t tile_batch_launch(int dtype, const void* insts, const TileBlock* blocks, long long nblocks,
+                             const void* fin, const void* forces, void* fout, const long long* step0, int step,
+                             int steps, hipStream_t st)
+{
+    if (dtype == DUGKS_F64)
+        tile_batch_t<double>(insts, blocks, nblocks, fin, forces, fout, step0, step, steps, st);
+    else
+        tile_batch_t<float>(insts, blocks, nblocks, fin, forces, fout, step0, step, steps, st);
+    return hipGetLastError();
+}
+
+// the workgroups of a launch of `steps` steps on instance `inst` of nx x ny cells
+void tile_blocks(int inst, int nx, int ny, int steps, std::vector<TileBlock>& out)
+{
+    const int ox = TILE_X - 2 * steps, oy = TILE_Y - 2 * steps;
+    for (int by = 0; by * oy < ny; ++by)
+        for (int bx = 0; bx * ox < nx; ++bx) out.push_back(TileBlock{inst, bx, by, 0});
+}
+
+}  // namespace dugks

@@ -99,4 +99,12 @@ __host__ __device__ constexpr int max_waves_per_eu()
 #define DUGKS_KERNEL_BOUNDS(NT, MINW, MAXW) \
     __attribute__((amdgpu_flat_work_group_size(1, NT), amdgpu_waves_per_eu(MINW, MAXW)))
 
+// the D2Q9 tile kernel takes 1 .. TILE_MAX_STEPS time steps per launch
+constexpr int TILE_MAX_STEPS = 6;
+
+// one workgroup of a batched launch of it: its instance and tile
+struct TileBlock {
+    int inst, bx, by, pad;
+};
+
 }  // namespace dugks
