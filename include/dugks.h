@@ -100,8 +100,8 @@ enum dugks_bc {
  *   bc[6]       side kinds; uw[6][3] wall velocities; pw[6] wall pressures
  *               (pressure p = (rho - rho0) RT)
  *   model       DUGKS_MODEL_INCOMPRESSIBLE (0, the paper's model) or
- *               DUGKS_MODEL_ORIGINAL (1: D2Q9 as the incompressible model, the
- *               3-D sets on the two-lane fused kernel where the incompressible
+ *               DUGKS_MODEL_ORIGINAL (1: in FP64 as the incompressible model, in
+ *               FP32 on the two-lane fused kernel where the incompressible
  *               model would take it and no force field is given, else on the
  *               general kernels; no batched form, no
  *               adjoint: DUGKS_EUNSUPPORTED there)
@@ -285,17 +285,17 @@ int dugks_init_vjp(dugks_ctx* ctx, const void* u, const void* force, double t0, 
 /* Which step kernel a launch without a force field uses (diagnostics):
  * 0 = general two-pass kernels, 1 = fused single launch with every
  * interface evaluated by both neighbouring cells, 2 = fused single launch
- * with every interface evaluated once, 3 = as 2, for D2Q9 on tiles with one
- * lane per cell (dugks_run then takes several steps per launch), for the 3-D
- * sets with the velocity set split over two lanes per column.  By default
- * each launch takes the faster one on MI355X: 3 for D2Q9 and D3Q27, for
- * D3Q19 FP64 without a force field and for D3Q19 FP32 on uniform meshes
- * without one; 2 otherwise.  The original-model variant uses 3 for D2Q9, for
- * the 3-D sets where the incompressible model would and no force field is
- * given, else 0.  A batch decides once for all its instances (uniform
+ * with every interface evaluated once, 3 = as 2, in FP64 with the cells'
+ * values in registers (D2Q9: tiles, of which dugks_run takes several steps per
+ * launch; 3-D: two lanes per column), in FP32 with the velocity set split over
+ * two lanes per column.  By default each launch takes the faster one on
+ * MI355X: FP64 3 always; FP32 3 for D2Q9 and D3Q27, and for D3Q19 on uniform
+ * meshes without a force field, 2 otherwise.  The original-model variant uses
+ * 3 in FP64, and in FP32 where the incompressible model would and no force
+ * field is given, else 0.  A batch decides once for all its instances (uniform
  * meshes, any force field), so batched and single-instance states are bitwise
  * equal when the instances share the mesh kind and the presence of a force
- * field; D2Q9 states always are.  All kernels give the same results to
+ * field; FP64 D2Q9 states always are.  All kernels give the same results to
  * rounding. */
 int dugks_kernel_variant(const dugks_ctx* ctx);
 
@@ -358,20 +358,21 @@ int dugks_batch_step(dugks_batch* b, void* f_in, void* f_out, const void* forces
 
 /*
  * Autotuner of the batched launch: times nsteps steps (after one warm-up
- * step) and keeps the fastest for later dugks_batch_run calls.  D2Q9: the
- * time steps of one launch, as the model of the batch's default has them
- * (tile variant 0), one fewer (1) or one more (2).  D3Q19: each instance's
- * own march chunk from the chunk model (the device's resident workgroups
- * shared among the instances in proportion to their cells; chunk 0, also
- * the batch's default), or one chunk of 4, 8, 16, 32 or 64 planes for all.  Results do not
+ * step) and keeps the fastest for later dugks_batch_run calls.  FP64 D2Q9:
+ * the time steps of one launch, as the model of the batch's default has them
+ * (tile variant 0), one fewer (1) or one more (2).  Else: every tile shape
+ * (D3Q19 one; FP32 D2Q9 rows of 128, 64 or 256 columns) and every chunk policy:
+ * each instance's own march chunk from the chunk model (the device's resident
+ * workgroups shared among the instances in proportion to their cells; chunk 0,
+ * also the batch's default), or one chunk of 4, 8, 16, 32 or 64 planes for all.  Results do not
  * depend on the choice (every interface is evaluated by the same code in
  * any tiling), so tuning never changes a state.
  *   f_a, f_b   two distinct caller-owned scratch buffers of the batch's
  *              size, holding a valid state (e.g. copies of the current
  *              one); both are overwritten
  *   forces, force_offsets  as in dugks_batch_run (the tuned workload)
- *   tile_out, chunk_out    nullable: the chosen tile variant (D2Q9) and
- *                          chunk policy (D3Q19; 0 = per-instance chunks)
+ *   tile_out, chunk_out    nullable: the chosen tile variant and chunk
+ *                          policy (0 = per-instance chunks)
  * Synchronises the stream; the batch clock is left unchanged.  Drops any
  * captured graph.  DUGKS_EINVAL for bad arguments or nsteps < 1.
  */

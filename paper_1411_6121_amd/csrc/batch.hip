@@ -14,19 +14,29 @@
 #include "march.hpp"
 
 namespace dugks {
-long long batch_resident_slots(int dtype, bool uniform, int n_cu);
-hipError_t batch_step_launch(int dtype, bool uniform, const void* insts, const long long* bstart,
-                             const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
-                             void* fout, const long long* step0, int step, hipStream_t st);
-void fused_tile_shape(int* bx, int* by);
-// the D2Q9 tile kernel
+// FP32: the marched kernels
+long long f32_batch_slots(int lattice, bool uniform, int variant, int n_cu);
+hipError_t f32_batch_launch(int lattice, bool uniform, int variant, const void* insts, const long long* bstart,
+                            const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
+                            void* fout, const long long* step0, int step, hipStream_t st);
+int fused_tile_variants(int lattice);
+void fused_tile_shape(int lattice, int variant, int* bx, int* by);
+// FP64 D3Q19: the row kernel
+template <class LAT, typename T>
+long long row_batch_slots(int n_cu);
+template <class LAT, typename T>
+void row_batch_launch(const void* insts, const long long* bstart, const BatchGeom* geom, int n, long long nblocks,
+                      const void* fin, const void* forces, void* fout, const long long* step0, int step, hipStream_t st);
+int row_chunk_of(long long tiles, int nz, long long slots);
+void row_tile_shape(int* bx, int* by);
+// FP64 D2Q9: the tile kernel
 long long tile_count(int nx, int ny, int steps);
-int tile_batch_steps(int dtype, int n, const int* nx, const int* ny, int n_cu);
+int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu);
 std::vector<int> tile_plan(int nsteps, int most);
 void tile_blocks(int inst, int nx, int ny, int steps, std::vector<TileBlock>& out);
-hipError_t tile_batch_launch(int dtype, const void* insts, const TileBlock* blocks, long long nblocks,
-                             const void* fin, const void* forces, void* fout, const long long* step0, int step,
-                             int steps, hipStream_t st);
+hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
+                             const void* forces, void* fout, const long long* step0, int step, int steps,
+                             hipStream_t st);
 
 // batch clock: set (reset != 0: s = add) or advance (s += add) the
 // device-side step counter (kernel nodes, so a captured run replays them)
@@ -58,11 +68,12 @@ using namespace dugks;
 
 struct dugks_batch {
     int n = 0, lattice = 0, dtype = 0, D = 0, Q = 0, esize = 0;
-    int chunk = 0;            // march chunk in use (0 = default)
-    int most = 1, model = 1;  // D2Q9: time steps of one launch, and the model's choice
-    TileBlock* tiles_dev[TILE_MAX_STEPS + 1] = {};  // D2Q9: the workgroups of a launch of s steps
-    long long tblocks[TILE_MAX_STEPS + 1] = {};  // D2Q9: workgroups of a launch of s steps
+    int tile = 0, chunk = 0;  // tile-shape variant and march chunk (0 = default) in use
     bool uniform = true;      // every instance on a uniform mesh
+    bool tiled = false;       // FP64 D2Q9: the tile kernel
+    int most = 1, model = 1;  // of it: time steps of one launch, and the model's choice
+    TileBlock* tiles_dev[TILE_MAX_STEPS + 1] = {};  // the workgroups of a launch of s steps
+    long long tblocks[TILE_MAX_STEPS + 1] = {};     // and how many they are
     bool any_field = false;   // some instance has a force field
     std::vector<dugks_config> cfgs;
     std::vector<std::vector<double>> faces_own;  // copies of custom face coordinates (cfgs[i].faces point here)
@@ -115,8 +126,8 @@ static int device_cus()
     return ncu;
 }
 
-// D2Q9: the workgroups of a launch of `steps` steps per instance, uploaded
-// when they change (synchronously, never inside a capture)
+// tile kernel: the workgroups of a launch of `steps` steps per instance, uploaded
+// on first use (synchronously, never inside a capture)
 static int set_tiles(dugks_batch* b, int steps)
 {
     if (b->tiles_dev[steps]) return DUGKS_OK;
@@ -129,7 +140,7 @@ static int set_tiles(dugks_batch* b, int steps)
     return DUGKS_OK;
 }
 
-// the D2Q9 launches of the batch take up to `most` steps each
+// the tile kernel's launches take up to `most` steps each
 static int set_most(dugks_batch* b, int most)
 {
     for (int s = 1; s <= most; ++s) {
@@ -154,25 +165,29 @@ static int choose_most(dugks_batch* b)
     }
     // (a table of workgroups also has to fit the host's memory)
     if (b->tblocks[1] > (1LL << 26)) return bfail(b, DUGKS_EUNSUPPORTED, "batch too large for one launch");
-    b->model = tile_batch_steps(b->dtype, b->n, nx.data(), ny.data(), device_cus());
+    b->model = tile_batch_steps(b->n, nx.data(), ny.data(), device_cus());
     while (b->tblocks[b->model] > (1LL << 26)) --b->model;
     return set_most(b, b->model);
 }
 
-// D3Q19: workgroup geometry of every instance for march chunk `chunk`: tile counts, chunk and the workgroup prefix sum;
+// Workgroup geometry of every instance for tile-shape variant `tile` and
+// march chunk `chunk`: tile counts, chunk and the workgroup prefix sum;
 // uploaded synchronously (never inside a capture).  chunk > 0: the same chunk
 // for every instance; chunk = 0: a chunk per instance from the chunk model
 // (auto_chunk) with the device's resident workgroups shared among the
 // instances in proportion to their cells, so that large instances march
 // long chunks (fewer recomputed halo planes) and small ones short chunks
 // (more workgroups at once).
-static int set_geometry(dugks_batch* b, int chunk)
+static int set_geometry(dugks_batch* b, int tile, int chunk)
 {
     const int n = b->n, D = b->D, M = D - 1;
     int bx, by;
-    fused_tile_shape(&bx, &by);
+    const bool f64 = b->dtype == DUGKS_F64;  // D3Q19 row kernel
+    if (f64) row_tile_shape(&bx, &by);
+    else fused_tile_shape(b->lattice, tile, &bx, &by);
     long long slots = 0;
-    if (chunk == 0) slots = batch_resident_slots(b->dtype, b->uniform, device_cus());
+    if (chunk == 0)
+        slots = f64 ? row_batch_slots<D3Q19, double>(device_cus()) : f32_batch_slots(b->lattice, b->uniform, tile, device_cus());
     std::vector<long long> bstart(n + 1, 0);
     std::vector<BatchGeom> geom(n);
     for (int i = 0; i < n; ++i) {
@@ -186,7 +201,8 @@ static int set_geometry(dugks_batch* b, int chunk)
             long long cells = 1;
             for (int a = 0; a < D; ++a) cells *= nn[a];
             const long long share = std::max(1LL, (long long)((double)slots * (double)cells / (double)b->ncells));
-            g.chunk = auto_chunk((long long)g.tiles0 * g.tiles1, nn[M], share);
+            const long long tiles = (long long)g.tiles0 * g.tiles1;
+            g.chunk = f64 ? row_chunk_of(tiles, nn[M], share) : auto_chunk(tiles, nn[M], share);
         }
         g.pad = 0;
         const int chunks = (nn[M] + g.chunk - 1) / g.chunk;
@@ -199,6 +215,7 @@ static int set_geometry(dugks_batch* b, int chunk)
         return bfail(b, DUGKS_EHIP, "batch geometry upload");
     drop_graph(b);
     b->nblocks = bstart[n];
+    b->tile = tile;
     b->chunk = chunk;
     return DUGKS_OK;
 }
@@ -238,7 +255,7 @@ static int build_tables(dugks_batch* b, const int64_t* offsets, hipStream_t st)
         hipMemcpy(b->cstart_dev, cstart.data(), sizeof(long long) * (n + 1), hipMemcpyHostToDevice) != hipSuccess)
         return bfail(b, DUGKS_EHIP, "batch table upload");
     (void)st;
-    return b->D == 2 ? choose_most(b) : set_geometry(b, 0);
+    return b->tiled ? choose_most(b) : set_geometry(b, 0, 0);
 }
 
 extern "C" int dugks_batch_create(const dugks_config* cfgs, int n, const int64_t* offsets, void* stream,
@@ -278,6 +295,7 @@ extern "C" int dugks_batch_create(const dugks_config* cfgs, int n, const int64_t
     for (int i = 0; i < n; ++i)
         for (int a = 0; a < b->D; ++a)
             if (cfgs[i].mesh[a] != DUGKS_UNIFORM) b->uniform = false;
+    b->tiled = b->D == 2 && b->dtype == DUGKS_F64;
     const int rc = b->dtype == DUGKS_F64 ? build_tables<double>(b, offsets, (hipStream_t)stream)
                                          : build_tables<float>(b, offsets, (hipStream_t)stream);
     if (rc != DUGKS_OK) {
@@ -314,11 +332,18 @@ static int batch_launch_any(dugks_batch* b, const void* fin, void* fout, const v
 {
     // without any field the field-free kernels run (as for single instances)
     const void* fz = b->any_field ? forces : nullptr;
-    const hipError_t e =
-        b->D == 2 ? tile_batch_launch(b->dtype, b->insts_dev, b->tiles_dev[steps], b->tblocks[steps], fin, fz, fout,
-                                      b->step_dev, step, steps, st)
-                  : batch_step_launch(b->dtype, b->uniform, b->insts_dev, b->bstart_dev, b->geom_dev, b->n,
-                                      b->nblocks, fin, fz, fout, b->step_dev, step, st);
+    hipError_t e = hipSuccess;
+    if (b->tiled) {
+        e = tile_batch_launch(b->insts_dev, b->tiles_dev[steps], b->tblocks[steps], fin, fz, fout, b->step_dev, step,
+                              steps, st);
+    } else if (b->dtype == DUGKS_F64) {
+        row_batch_launch<D3Q19, double>(b->insts_dev, b->bstart_dev, b->geom_dev, b->n, b->nblocks, fin, fz, fout,
+                                        b->step_dev, step, st);
+        e = hipGetLastError();
+    } else {
+        e = f32_batch_launch(b->lattice, b->uniform, b->tile, b->insts_dev, b->bstart_dev, b->geom_dev, b->n, b->nblocks,
+                             fin, fz, fout, b->step_dev, step, st);
+    }
     return e == hipSuccess ? DUGKS_OK : bfail(b, DUGKS_EHIP, hipGetErrorString(e));
 }
 
@@ -344,7 +369,7 @@ static int launch_plan(dugks_batch* b, const void* f_in, void* f_out, const void
 
 static int launch_run(dugks_batch* b, const void* f_in, void* f_out, const void* forces, int nsteps, hipStream_t st)
 {
-    return launch_plan(b, f_in, f_out, forces, tile_plan(nsteps, b->D == 2 ? b->most : 1), st);
+    return launch_plan(b, f_in, f_out, forces, tile_plan(nsteps, b->tiled ? b->most : 1), st);
 }
 
 // per-instance force offsets into the instance table (before any launch)
@@ -452,7 +477,7 @@ extern "C" int dugks_batch_tune(dugks_batch* b, void* f_a, void* f_b, const void
         ms /= (float)steps;
         return r;
     };
-    if (b->D == 2) {
+    if (b->tiled) {
         // 0: the model's steps per launch; 1: one fewer; 2: one more
         int best_steps = b->model;
         for (int tile = 0; tile < 3 && rc == DUGKS_OK; ++tile) {
@@ -468,20 +493,23 @@ extern "C" int dugks_batch_tune(dugks_batch* b, void* f_a, void* f_b, const void
     } else {
         // 0: a chunk per instance from the chunk model; else one chunk for all
         static const int chunks[] = {0, 4, 8, 16, 32, 64};
-        for (int chunk : chunks) {
-            if (chunk > 2 * maxm) continue;
-            float ms = 0.0f;
-            rc = set_geometry(b, chunk);
-            if (rc == DUGKS_OK) rc = timed(1, ms);
-            if (rc != DUGKS_OK) break;
-            if (best < 0.0f || ms < best) { best = ms; best_chunk = chunk; }
+        const int shapes = b->dtype == DUGKS_F64 ? 1 : fused_tile_variants(b->lattice);
+        for (int tile = 0; tile < shapes && rc == DUGKS_OK; ++tile) {
+            for (int chunk : chunks) {
+                if (chunk > 2 * maxm) continue;
+                float ms = 0.0f;
+                rc = set_geometry(b, tile, chunk);
+                if (rc == DUGKS_OK) rc = timed(1, ms);
+                if (rc != DUGKS_OK) break;
+                if (best < 0.0f || ms < best) { best = ms; best_tile = tile; best_chunk = chunk; }
+            }
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != DUGKS_OK) return rc;
-    if (b->D == 3) {
-        rc = set_geometry(b, best_chunk);
+    if (!b->tiled) {
+        rc = set_geometry(b, best_tile, best_chunk);
         if (rc != DUGKS_OK) return rc;
     }
     hipLaunchKernelGGL(k_batch_clock, dim3(1), dim3(1), 0, st, b->step_dev, clock, 1);

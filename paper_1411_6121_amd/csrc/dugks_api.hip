@@ -251,6 +251,7 @@ void fill_inst(const dugks_config* c, Inst<T>& P, T* met_dev, std::vector<T>& me
         for (int a = 0; a < 3; ++a) P.uw[s][a] = (T)(a < D ? c->uw[s][a] : 0.0);
         P.rhow[s] = (T)(c->rho0 + c->pw[s] / c->RT);
         P.rhowo[s] = (T)(c->pw_osc[s] / c->RT);
+        if (P.rhowo[s] != T(0)) P.osc = 1;
     }
     P.omega = c->omega;
     P.phase = c->phase;
@@ -669,7 +670,7 @@ extern "C" int dugks_step(dugks_ctx* ctx, const void* f_in, void* f_out, const v
 }
 
 namespace dugks {
-int resolve_step_kernel(const dugks_ctx* ctx, bool field);
+int step_kernel(const dugks_ctx* ctx, bool field);
 int tile_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0, int nsteps, hipStream_t st,
              int* which_out);
 }  // namespace dugks
@@ -679,10 +680,10 @@ extern "C" int dugks_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force
 {
     if (!ctx) return fail(nullptr, DUGKS_EINVAL, "null context");
     if (nsteps < 0) return fail(ctx, DUGKS_EINVAL, "negative step count");
-    // D2Q9 on its default kernel: several steps per launch (a single step, and
+    // FP64 D2Q9 on its default kernel: several steps per launch (a single step, and
     // every error case, as dugks_step has them)
-    if (nsteps > 1 && ctx->cfg.lattice == DUGKS_D2Q9 && f_a && f_b && f_a != f_b && std::isfinite(t0) &&
-        std::isfinite(t0 + (nsteps - 1) * ctx->cfg.dt) && dugks::resolve_step_kernel(ctx, force != nullptr) == 3)
+    if (nsteps > 1 && ctx->cfg.lattice == DUGKS_D2Q9 && ctx->cfg.dtype == DUGKS_F64 && f_a && f_b && f_a != f_b && std::isfinite(t0) &&
+        std::isfinite(t0 + (nsteps - 1) * ctx->cfg.dt) && dugks::step_kernel(ctx, force != nullptr) == 3)
         return dugks::tile_run(ctx, f_a, f_b, force, t0, nsteps, (hipStream_t)stream, which_out);
     void* cur = f_a;
     void* nxt = f_b;
@@ -749,7 +750,7 @@ extern "C" int dugks_velocity_change(dugks_ctx* ctx, const void* f_a, const void
     return DUGKS_OK;
 }
 
-extern "C" int dugks_kernel_variant(const dugks_ctx* ctx) { return ctx ? dugks::resolve_step_kernel(ctx, false) : -1; }
+extern "C" int dugks_kernel_variant(const dugks_ctx* ctx) { return ctx ? dugks::step_kernel(ctx, false) : -1; }
 
 extern "C" void dugks_destroy(dugks_ctx* ctx)
 {

@@ -76,6 +76,7 @@ struct Inst {
     T uw[6][3];
     T rhow[6];     // rho0 + p_w / RT (pressure condition)
     T rhowo[6];    // oscillating part of the wall density: p_w,osc / RT
+    int osc;       // some wall density oscillates
     T rlo[3], rhi[3]; // ghost(-1) = (1-rlo) phi(0) + rlo phi(1); ghost(n) likewise
     double omega, phase;
     double gphase; // cos(phase): the time factor of a constant acceleration (omega = 0)
@@ -91,8 +92,15 @@ struct BatchGeom {
 template <typename T>
 __host__ __device__ inline T tfac(const Inst<T>& P, double t)
 {
-    if (P.omega == 0.0) return (T)P.gphase;
     return (T)cos(P.omega * t + P.phase);
+}
+
+// the same without the cosine where the acceleration is constant
+template <typename T>
+__device__ __forceinline__ T tfac_dev(const Inst<T>& P, double t)
+{
+    if (P.omega == 0.0) return (T)P.gphase;
+    return tfac(P, t);
 }
 
 // density of the pressure condition of Eq. (NEQ) on side s, rho0 +

@@ -611,32 +611,34 @@ static int launch_fused2(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void
     return launch_fused2_ff<LAT, T, BX, BY, MINW, PF, false, false>(ctx, P, fin, fout, force, t, st, chunk);
 }
 
-// Default step kernel (measured on MI355X, 128^3 D3Q19 and 1024^2 D2Q9
-// cavities).  The two-lane split (3) doubles the waves per SIMD of the D3Q19
-// tile and wins wherever its registers fit the occupancy it is built for;
-// with a force field its face-force interpolation spills (D3Q19 FP64), and
-// in FP32 only the uniform field-free instance fits four waves per SIMD, so
-// those cases take the one-lane kernel (2).  D2Q9 and D3Q27: the split
-// everywhere.
-int default_step_kernel(int lattice, int dtype, bool uniform, bool field)
-{
-    if (lattice == DUGKS_D2Q9 || lattice == DUGKS_D3Q27) return 3;
-    if (dtype == DUGKS_F64) return field ? 2 : 3;
-    return (uniform && !field) ? 3 : 2;
-}
-
-int split_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t, hipStream_t st, int chunk);
 int tile_steps(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t0, long long k0, int steps,
                hipStream_t st);
+template <class LAT, typename T>
+int row_step(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t, hipStream_t st,
+             int chunk);
+int split_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t, hipStream_t st, int chunk);
+
+// Default FP32 step kernel: the two-lane march (3) where its registers fit the
+// occupancy it is built for, which D3Q19 does on uniform meshes without a force
+// field only, else the one-lane march (2).  (FP64 takes the register kernels,
+// kernels_tile.hip and row3.hpp.  In FP32 they run 1.2 to 2 times as fast as
+// these as well, but round differently, and FP32 states and their totals are
+// kept bit for bit.)
+static int default_f32_kernel(int lattice, bool uniform, bool field)
+{
+    if (lattice == DUGKS_D2Q9 || lattice == DUGKS_D3Q27) return 3;
+    return (uniform && !field) ? 3 : 2;
+}
 
 int setup_fast(dugks_ctx* ctx)
 {
     ctx->fast = 0;
     const char* env = getenv("DUGKS_FORCE_GENERAL");
     if (env && env[0] == '1') return DUGKS_OK;
-    // 1: every face evaluated by both neighbours; 2: faces evaluated once;
-    // 3: faces once, velocity set split over two lanes per column;
-    // 4: per launch, the default of default_step_kernel
+    // 1: every face evaluated by both neighbours; 2: faces evaluated once (one
+    // lane per column of a marched tile); 3: in FP64 the register kernels
+    // (kernels_tile.hip, row3.hpp), in FP32 the two-lane march; 4: per launch,
+    // the default (FP64: 3, FP32: default_f32_kernel)
     ctx->fast = 4;
     const char* v = getenv("DUGKS_FUSED_VARIANT");
     if (v && v[0] == '1') ctx->fast = 1;
@@ -648,72 +650,81 @@ int setup_fast(dugks_ctx* ctx)
     return DUGKS_OK;
 }
 
-// the step kernel a launch with (without) a force field uses
-int resolve_step_kernel(const dugks_ctx* ctx, bool field)
+// the step kernel of a launch with (without) a force field
+int step_kernel(const dugks_ctx* ctx, bool field)
 {
-    // the original-model variant: the two-lane kernel where it is the
-    // incompressible choice and no force field is given, else the general
-    // kernels
-    if (ctx->cfg.model != DUGKS_MODEL_INCOMPRESSIBLE) {
-        if (ctx->fast == 0) return 0;
-        if (ctx->cfg.lattice == DUGKS_D2Q9) return ctx->fast == 4 || ctx->fast == 3 ? 3 : 0;
-        if (field) return 0;
-        if (ctx->cfg.lattice == DUGKS_D3Q27) return 3;
-        const bool uni = ctx->cfg.dtype == DUGKS_F64 ? ctx->pd.uni != 0 : ctx->pf.uni != 0;
-        const int v = ctx->fast != 4 ? ctx->fast : default_step_kernel(ctx->cfg.lattice, ctx->cfg.dtype, uni, false);
-        return v == 3 ? 3 : 0;
+    const int lat = ctx->cfg.lattice, f = ctx->fast;
+    const bool orig = ctx->cfg.model != DUGKS_MODEL_INCOMPRESSIBLE;
+    if (f == 0) return 0;
+    if (ctx->cfg.dtype == DUGKS_F64) {
+        if (f >= 3 || lat == DUGKS_D3Q27) return 3;
+        return orig ? 0 : f;  // 1 and 2 know the incompressible model only
     }
-    // D3Q27 has the split kernel only (the one-lane tile would not fit a CU)
-    if (ctx->cfg.lattice == DUGKS_D3Q27) return ctx->fast == 0 ? 0 : 3;
-    if (ctx->fast != 4) return ctx->fast;
-    const bool uni = ctx->cfg.dtype == DUGKS_F64 ? ctx->pd.uni != 0 : ctx->pf.uni != 0;
-    return default_step_kernel(ctx->cfg.lattice, ctx->cfg.dtype, uni, field);
+    // the original-model variant: the two-lane march where it is the
+    // incompressible choice and no force field is given, else the general kernels
+    if (orig && field) return 0;
+    // D3Q27 has the two-lane march only (the one-lane tile would not fit a CU)
+    if (lat == DUGKS_D3Q27) return 3;
+    const int k = f != 4 ? f : default_f32_kernel(lat, ctx->pf.uni != 0, field);
+    return orig && k != 3 ? 0 : k;
 }
 
 int fast_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t, hipStream_t st, bool* handled)
 {
-    *handled = false;
-    const int variant = resolve_step_kernel(ctx, force != nullptr);
-    if (variant < 1 || variant > 3) return DUGKS_OK;
-    *handled = true;
+    const int variant = step_kernel(ctx, force != nullptr);
+    *handled = variant != 0;
+    if (variant == 0) return DUGKS_OK;
+    const int chunk = ctx->chunk;  // 0: chosen per launch
+    const bool f64 = ctx->cfg.dtype == DUGKS_F64;
+    if (variant == 3) {
+        if (!f64) return split_step(ctx, fin, fout, force, t, st, chunk);
+        if (ctx->cfg.lattice == DUGKS_D2Q9) return tile_steps(ctx, fin, fout, force, t, 0, 1, st);
+        if (ctx->cfg.lattice == DUGKS_D3Q19) return row_step<D3Q19, double>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
+        return row_step<D3Q27, double>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
+    }
     // tiles: D3Q19 18 x 14 columns (16 x 12 interior), D2Q9 rows of 128
     // columns (126 interior)
-    const int chunk = ctx->chunk;  // 0: chosen per launch (auto_chunk)
-    if (variant == 3 && ctx->cfg.lattice == DUGKS_D2Q9) return tile_steps(ctx, fin, fout, force, t, 0, 1, st);
-    if (variant == 3) return split_step(ctx, fin, fout, force, t, st, chunk);
     if (variant == 2) {
         if (ctx->cfg.lattice == DUGKS_D3Q19) {
-            if (ctx->cfg.dtype == DUGKS_F64) return launch_fused2<D3Q19, double, 18, 14, 1, prefetch_planes<D3Q19, double>()>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
+            if (f64) return launch_fused2<D3Q19, double, 18, 14, 1, prefetch_planes<D3Q19, double>()>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
             return launch_fused2<D3Q19, float, 18, 14, 2, prefetch_planes<D3Q19, float>()>(ctx, ctx->pf, fin, fout, force, t, st, chunk);
         }
-        if (ctx->cfg.dtype == DUGKS_F64) return launch_fused2<D2Q9, double, 128, 1, 2, prefetch_planes<D2Q9, double>()>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
+        if (f64) return launch_fused2<D2Q9, double, 128, 1, 2, prefetch_planes<D2Q9, double>()>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
         return launch_fused2<D2Q9, float, 128, 1, 2, prefetch_planes<D2Q9, float>()>(ctx, ctx->pf, fin, fout, force, t, st, chunk);
     }
     if (ctx->cfg.lattice == DUGKS_D3Q19) {
-        if (ctx->cfg.dtype == DUGKS_F64) return launch_fused<D3Q19, double, 18, 14, 1>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
+        if (f64) return launch_fused<D3Q19, double, 18, 14, 1>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
         return launch_fused<D3Q19, float, 18, 14, 2>(ctx, ctx->pf, fin, fout, force, t, st, chunk);
     }
-    if (ctx->cfg.dtype == DUGKS_F64) return launch_fused<D2Q9, double, 128, 1, 2>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
+    if (f64) return launch_fused<D2Q9, double, 128, 1, 2>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
     return launch_fused<D2Q9, float, 128, 1, 2>(ctx, ctx->pf, fin, fout, force, t, st, chunk);
 }
 
 void release_fast(dugks_ctx*) {}
 
-// Tile of the batched D3Q19 kernels: columns along x and y incl. halo (18 x
-// 14: the FP64 LDS ring fills a CU)
-void fused_tile_shape(int* bx, int* by)
+// Tile shapes of the batched FP32 kernels: (columns along x, along y) incl. halo.
+// D3Q19 has one (18 x 14); D2Q9 rows of 128 (default), 64 or 256 columns, chosen
+// per batch by the autotuner.
+int fused_tile_variants(int lattice) { return lattice == DUGKS_D3Q19 ? 1 : 3; }
+
+void fused_tile_shape(int lattice, int variant, int* bx, int* by)
 {
-    *bx = 18;
-    *by = 14;
+    if (lattice == DUGKS_D3Q19) {
+        *bx = 18;
+        *by = 14;
+        return;
+    }
+    *bx = variant == 1 ? 64 : (variant == 2 ? 256 : 128);
+    *by = 1;
 }
 
-template <class LAT, typename T, int BX, int BY, int MINW, bool PF, bool FF>
+template <bool FF>
 static hipError_t fused2_batch_ff(const void* insts, const long long* bstart, const BatchGeom* geom, int n,
                                   long long nblocks, const void* fin, const void* forces, void* fout,
                                   const long long* step0, int step, hipStream_t st)
 {
-    auto kern = k_fused2_batch<LAT, T, BX, BY, MINW, PF, FF>;
-    const size_t lds = fused2_lds<LAT, T, BX, BY>();
+    auto kern = k_fused2_batch<D3Q19, float, 18, 14, 2, prefetch_planes<D3Q19, float>(), FF>;
+    const size_t lds = fused2_lds<D3Q19, float, 18, 14>();
     static bool attr = false;
     if (!attr) {
         const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -721,57 +732,37 @@ static hipError_t fused2_batch_ff(const void* insts, const long long* bstart, co
         attr = true;
     }
     if (nblocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(BX * BY), lds, st, (const Inst<T>*)insts, bstart, geom, n,
-                       (const T*)fin, (const T*)forces, (T*)fout, step0, step);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(18 * 14), lds, st, (const Inst<float>*)insts, bstart, geom, n,
+                       (const float*)fin, (const float*)forces, (float*)fout, step0, step);
     return hipGetLastError();
 }
 
-template <class LAT, typename T, int BX, int BY, int MINW>
-static hipError_t fused2_batch_t(const void* insts, const long long* bstart, const BatchGeom* geom, int n,
-                                 long long nblocks, const void* fin, const void* forces, void* fout,
-                                 const long long* step0, int step, hipStream_t st)
+hipError_t split_batch_launch(int lattice, int variant, const void* insts, const long long* bstart,
+                              const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
+                              void* fout, const long long* step0, int step, hipStream_t st);
+
+long long split_batch_slots(int lattice, int variant, int n_cu);
+
+// workgroups of the batched FP32 step kernel (the one f32_batch_launch takes)
+// resident on the device at once
+long long f32_batch_slots(int lattice, bool uniform, int variant, int n_cu)
 {
-    constexpr bool PF = prefetch_planes<LAT, T>();
-    if (forces)
-        return fused2_batch_ff<LAT, T, BX, BY, MINW, PF, true>(insts, bstart, geom, n, nblocks, fin, forces, fout,
-                                                               step0, step, st);
-    return fused2_batch_ff<LAT, T, BX, BY, MINW, PF, false>(insts, bstart, geom, n, nblocks, fin, forces, fout, step0,
-                                                            step, st);
+    if (default_f32_kernel(lattice, uniform, false) == 3) return split_batch_slots(lattice, variant, n_cu);
+    constexpr bool PF = prefetch_planes<D3Q19, float>();
+    return resident_slots(k_fused2_batch<D3Q19, float, 18, 14, 2, PF, false>, 18 * 14, fused2_lds<D3Q19, float, 18, 14>(),
+                          n_cu);
 }
 
-hipError_t split_batch_launch(int dtype, const void* insts, const long long* bstart, const BatchGeom* geom, int n,
-                              long long nblocks, const void* fin, const void* forces, void* fout,
-                              const long long* step0, int step, hipStream_t st);
-
-long long split_batch_slots(int dtype, int n_cu);
-
-template <class LAT, typename T, int BX, int BY, int MINW>
-static long long fused2_batch_slots_t(int n_cu)
+// one batched FP32 step on the default step kernel of the lattice (so that
+// batched and single-instance runs give identical states)
+hipError_t f32_batch_launch(int lattice, bool uniform, int variant, const void* insts, const long long* bstart,
+                            const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
+                            void* fout, const long long* step0, int step, hipStream_t st)
 {
-    constexpr bool PF = prefetch_planes<LAT, T>();
-    return resident_slots(k_fused2_batch<LAT, T, BX, BY, MINW, PF, false>, BX * BY, fused2_lds<LAT, T, BX, BY>(), n_cu);
-}
-
-// workgroups of the batched D3Q19 step kernel (the one batch_step_launch
-// takes) resident on the device at once
-long long batch_resident_slots(int dtype, bool uniform, int n_cu)
-{
-    if (default_step_kernel(DUGKS_D3Q19, dtype, uniform, false) == 3) return split_batch_slots(dtype, n_cu);
-    return dtype == DUGKS_F64 ? fused2_batch_slots_t<D3Q19, double, 18, 14, 1>(n_cu)
-                              : fused2_batch_slots_t<D3Q19, float, 18, 14, 2>(n_cu);
-}
-
-// one batched D3Q19 step on the default step kernel of the precision (so that
-// batched and single-instance runs take the same kernel)
-hipError_t batch_step_launch(int dtype, bool uniform, const void* insts, const long long* bstart,
-                             const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
-                             void* fout, const long long* step0, int step, hipStream_t st)
-{
-    if (default_step_kernel(DUGKS_D3Q19, dtype, uniform, forces != nullptr) == 3)
-        return split_batch_launch(dtype, insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st);
-    if (dtype == DUGKS_F64)
-        return fused2_batch_t<D3Q19, double, 18, 14, 1>(insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st);
-    return fused2_batch_t<D3Q19, float, 18, 14, 2>(insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st);
+    if (default_f32_kernel(lattice, uniform, forces != nullptr) == 3)
+        return split_batch_launch(lattice, variant, insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st);
+    if (forces) return fused2_batch_ff<true>(insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st);
+    return fused2_batch_ff<false>(insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st);
 }
 
 }  // namespace dugks

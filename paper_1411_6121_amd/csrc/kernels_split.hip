@@ -22,128 +22,10 @@
 #include "ctx.hpp"
 #include "kernels_general.hpp"
 #include "march.hpp"
+#include "wave.hpp"
 
 namespace dugks {
 
-
-// value of the partner lane (same column, other half): v_permlane32_swap
-// exchanges lanes 32..63 of its first operand with lanes 0..31 of its second;
-// with both operands = v the partner's value is the second result in the
-// lower half-wave and the first in the upper one.  Both lanes of a pair are
-// always active together.
-__device__ __forceinline__ unsigned partner_u32(unsigned v)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return __lane_id() < 32 ? r[1] : r[0];
-}
-__device__ __forceinline__ float partner(float v)
-{
-    return __builtin_bit_cast(float, partner_u32(__builtin_bit_cast(unsigned, v)));
-}
-__device__ __forceinline__ double partner(double v)
-{
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = partner_u32((unsigned)b), hi = partner_u32((unsigned)(b >> 32));
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
-// Lane-pair sums of two values at once: v_permlane32_swap(a, b) leaves
-// (a(l), b(l-32)) in its first result and (a(l+32), b(l)) in its second, so
-// one add gives the pair sum of a in the lower half-wave and that of b in
-// the upper one; a second swap of that sum with a copy of itself hands both
-// halves to every lane.  Each sum is the lower lane's value plus the upper
-// one's, bitwise what both lanes get from v + partner(v).  The copy is made
-// opaque to the compiler so that the swap never sees two equal operands.
-__device__ __forceinline__ void pair_sum2_u32(unsigned a, unsigned b, unsigned& r0, unsigned& r1)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    r0 = r[0];
-    r1 = r[1];
-}
-// M: how the pair is combined: 0 both sums plain; 1 a plain, b signed (the
-// lane's sign sg, +1 in the lower and -1 in the upper half-wave); 2 both
-// signed.  A signed sum is that of sg * x: the lower lane's value minus the
-// upper one's, bitwise what sg * x + partner(sg * x) gives, since
-// multiplying by -1 is exact.
-template <int M>
-__device__ __forceinline__ float pair_combine(float x0, float x1, float sg)
-{
-    if constexpr (M == 0) return x0 + x1;
-    else if constexpr (M == 1) return __builtin_fmaf(sg, x1, x0);
-    else return x0 - x1;
-}
-template <int M>
-__device__ __forceinline__ double pair_combine(double x0, double x1, double sg)
-{
-    if constexpr (M == 0) return x0 + x1;
-    else if constexpr (M == 1) return __builtin_fma(sg, x1, x0);
-    else return x0 - x1;
-}
-template <int M = 0>
-__device__ __forceinline__ void pair_sum2(float a, float b, float& sa, float& sb, float sg = 1.0f)
-{
-    unsigned x0, x1;
-    pair_sum2_u32(__float_as_uint(a), __float_as_uint(b), x0, x1);
-    const float sum = pair_combine<M>(__uint_as_float(x0), __uint_as_float(x1), sg);
-    unsigned c = __float_as_uint(sum);
-    asm volatile("" : "+v"(c));
-    unsigned y0, y1;
-    pair_sum2_u32(__float_as_uint(sum), c, y0, y1);
-    sa = __uint_as_float(y0);
-    sb = __uint_as_float(y1);
-}
-template <int M = 0>
-__device__ __forceinline__ void pair_sum2(double a, double b, double& sa, double& sb, double sg = 1.0)
-{
-    const unsigned long long ua = (unsigned long long)__double_as_longlong(a);
-    const unsigned long long ub = (unsigned long long)__double_as_longlong(b);
-    unsigned l0, l1, h0, h1;
-    pair_sum2_u32((unsigned)ua, (unsigned)ub, l0, l1);
-    pair_sum2_u32((unsigned)(ua >> 32), (unsigned)(ub >> 32), h0, h1);
-    const double sum = pair_combine<M>(__longlong_as_double((long long)(((unsigned long long)h0 << 32) | l0)),
-                                       __longlong_as_double((long long)(((unsigned long long)h1 << 32) | l1)), sg);
-    const unsigned long long us = (unsigned long long)__double_as_longlong(sum);
-    unsigned clo = (unsigned)us, chi = (unsigned)(us >> 32);
-    asm volatile("" : "+v"(clo), "+v"(chi));
-    pair_sum2_u32((unsigned)us, clo, l0, l1);
-    pair_sum2_u32((unsigned)(us >> 32), chi, h0, h1);
-    sa = __longlong_as_double((long long)(((unsigned long long)h0 << 32) | l0));
-    sb = __longlong_as_double((long long)(((unsigned long long)h1 << 32) | l1));
-}
-// the moments of a column from the two lanes' partial sums: rho = rh + rh
-// of the partner lane, j[a] = the pair sum of sg * sj[a]
-template <int D, typename T>
-__device__ __forceinline__ void moment_sums(T rh, const T (&sj)[3], T sg, T& rho, T (&j)[3])
-{
-    pair_sum2<1>(rh, sj[0], rho, j[0], sg);
-    if constexpr (D == 3) {
-        pair_sum2<2>(sj[1], sj[2], j[1], j[2], sg);
-    } else {
-        const T x = sg * sj[1];
-        j[1] = x + partner(x);
-    }
-}
-
-// value of lane l + N (N > 0) or l - N (N < 0) of the lane's 16-lane row
-// (DPP row shift; a source outside the row leaves an unspecified value)
-template <int N>
-__device__ __forceinline__ unsigned row_shift_u32(unsigned v)
-{
-    constexpr int ctrl = N > 0 ? 0x100 + N : 0x110 - N;  // row_shl:N / row_shr:-N
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, false);
-}
-template <int N>
-__device__ __forceinline__ float row_shift(float v)
-{
-    return __uint_as_float(row_shift_u32<N>(__float_as_uint(v)));
-}
-template <int N>
-__device__ __forceinline__ double row_shift(double v)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = row_shift_u32<N>((unsigned)b), hi = row_shift_u32<N>((unsigned)(b >> 32));
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
 
 // number of half-0 velocities crossing a face of axis A, and the slot of k
 template <class LAT, int A>
@@ -1157,27 +1039,14 @@ static int launch_split(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void*
 
 int split_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t, hipStream_t st, int chunk)
 {
-    if (ctx->cfg.lattice == DUGKS_D3Q27) {
-        // 27 velocities, 16 x 8 column tiles.  FP64: the tile's LDS ring
-        // (120 KB) fills a CU, four waves (one per SIMD) whose state fits the
-        // register file without scratch; an 18 x 9 tile (six waves) would
-        // spill to scratch.  FP32: 60 KB, so two workgroups (eight waves)
-        // share a CU, where an 18 x 9 tile (76 KB, six waves at over 170
-        // registers) leaves one.
-        if (ctx->cfg.dtype == DUGKS_F64)
-            return launch_split<D3Q27, double, 16, 8, 1, false>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
+    // D3Q27: 16 x 8 column tiles, 60 KB of LDS, two workgroups (eight waves)
+    // share a CU, where an 18 x 9 tile (76 KB, six waves at over 170
+    // registers) leaves one
+    if (ctx->cfg.lattice == DUGKS_D3Q27)
         return launch_split<D3Q27, float, 16, 8, 2, false>(ctx, ctx->pf, fin, fout, force, t, st, chunk);
-    }
-    if (ctx->cfg.lattice == DUGKS_D3Q19) {
-        // FP64: a 16 x 8 column tile (78 KB of LDS) lets two workgroups share
-        // a CU, so one waits at its barriers while the other computes; that
-        // outweighs the larger halo share of the smaller tile (0.499 vs
-        // 0.515 ms at 128^3 with 18 x 14)
-        if (ctx->cfg.dtype == DUGKS_F64)
-            return launch_split<D3Q19, double, 16, 8, 2, false>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
+    if (ctx->cfg.lattice == DUGKS_D3Q19)
         return launch_split<D3Q19, float, 18, 14, 2, false>(ctx, ctx->pf, fin, fout, force, t, st, chunk);
-    }
-    return fail(ctx, DUGKS_EUNSUPPORTED, "no two-lane kernel of this lattice");
+    return launch_split<D2Q9, float, 128, 1, 2, false>(ctx, ctx->pf, fin, fout, force, t, st, chunk);
 }
 
 template <class LAT, typename T, int BX, int BY, int MINW, bool PF, bool FF>
@@ -1219,21 +1088,28 @@ static long long split_batch_slots_t(int n_cu)
 }
 
 // workgroups of the batched two-lane kernel resident on the device at once
-long long split_batch_slots(int dtype, int n_cu)
+long long split_batch_slots(int lattice, int variant, int n_cu)
 {
-    return dtype == DUGKS_F64 ? split_batch_slots_t<D3Q19, double, 18, 14, 1, false>(n_cu)
-                              : split_batch_slots_t<D3Q19, float, 18, 14, 2, false>(n_cu);
+    if (lattice == DUGKS_D2Q9) {
+        if (variant == 1) return split_batch_slots_t<D2Q9, float, 64, 1, 2, false>(n_cu);
+        if (variant == 2) return split_batch_slots_t<D2Q9, float, 256, 1, 2, false>(n_cu);
+        return split_batch_slots_t<D2Q9, float, 128, 1, 2, false>(n_cu);
+    }
+    return split_batch_slots_t<D3Q19, float, 18, 14, 2, false>(n_cu);
 }
 
-hipError_t split_batch_launch(int dtype, const void* insts, const long long* bstart, const BatchGeom* geom, int n,
-                              long long nblocks, const void* fin, const void* forces, void* fout,
-                              const long long* step0, int step, hipStream_t st)
+hipError_t split_batch_launch(int lattice, int variant, const void* insts, const long long* bstart,
+                              const BatchGeom* geom, int n, long long nblocks, const void* fin, const void* forces,
+                              void* fout, const long long* step0, int step, hipStream_t st)
 {
-    if (dtype == DUGKS_F64)
-        return split_batch_launch_t<D3Q19, double, 18, 14, 1, false>(insts, bstart, geom, n, nblocks, fin, forces, fout,
-                                                                     step0, step, st);
-    return split_batch_launch_t<D3Q19, float, 18, 14, 2, false>(insts, bstart, geom, n, nblocks, fin, forces, fout,
-                                                                step0, step, st);
+#define DUGKS_SPLIT_ARGS insts, bstart, geom, n, nblocks, fin, forces, fout, step0, step, st
+    if (lattice == DUGKS_D2Q9) {
+        if (variant == 1) return split_batch_launch_t<D2Q9, float, 64, 1, 2, false>(DUGKS_SPLIT_ARGS);
+        if (variant == 2) return split_batch_launch_t<D2Q9, float, 256, 1, 2, false>(DUGKS_SPLIT_ARGS);
+        return split_batch_launch_t<D2Q9, float, 128, 1, 2, false>(DUGKS_SPLIT_ARGS);
+    }
+    return split_batch_launch_t<D3Q19, float, 18, 14, 2, false>(DUGKS_SPLIT_ARGS);
+#undef DUGKS_SPLIT_ARGS
 }
 
 }  // namespace dugks

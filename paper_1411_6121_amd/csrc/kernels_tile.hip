@@ -1,4 +1,4 @@
-// kernels_tile.hip -- the D2Q9 step on tiles of 32 x 16 cells, one lane per
+// kernels_tile.hip -- the FP64 D2Q9 step on tiles of 32 x 16 cells, one lane per
 // cell, several time steps per launch.
 //
 // A workgroup loads a tile of the state into registers and advances it S
@@ -19,11 +19,10 @@
 // waves a tile) on meshes that fill the chip, the latency of one tile's chain
 // on small ones; the state crosses memory once per launch.  us a step, against
 // the kernel that marches rows of 128 columns with two lanes per column, one
-// step per launch: 1024^2 cavity FP64 28.7 against 52.7 and FP32 18 against
-// 37, 128^2 stretched cavity FP64 3.5 against 8.95, 40 x 20 channel FP64 3.8
+// step per launch: 1024^2 cavity FP64 28.7 against 52.7, 128^2 stretched cavity FP64 3.5 against 8.95, 40 x 20 channel FP64 3.8
 // against 8.9, 64 uneven instances FP64 126 against 175.  A march along y with
 // the rows in registers and no LDS (one lane per column, one step per launch)
-// took 41, 26, 8.5 and 8.3.
+// took 41, 8.5 and 8.3 for the first three.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -392,7 +391,7 @@ __global__ TILE_BOUNDS((SMALL ? 2 : 4)) void k_tile(const Inst<T>* __restrict__ 
     if (!SMALL && tile_no_wall(P, steps, bx, by))
         tile_body<T, UNI, ACC, FIELD, ORIG, true, false>(P, fin, force, fout, t0, k0, steps, bx, by, lds);
     else
-        tile_body<T, UNI, ACC, FIELD, ORIG, false, !SMALL && sizeof(T) == 8>(P, fin, force, fout, t0, k0, steps, bx, by, lds);
+        tile_body<T, UNI, ACC, FIELD, ORIG, false, false>(P, fin, force, fout, t0, k0, steps, bx, by, lds);
 }
 
 // many instances in one launch: blocks[b] is the instance and the tile of
@@ -415,10 +414,10 @@ __global__ TILE_BOUNDS(4) void k_tile_batch(const Inst<T>* __restrict__ insts, c
     fout += P.off;
     if (P.uni) {
         if (nw) tile_body<T, true, true, FIELD, false, true, false>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
-        else tile_body<T, true, true, FIELD, false, false, sizeof(T) == 8>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+        else tile_body<T, true, true, FIELD, false, false, true>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
     } else {
         if (nw) tile_body<T, false, true, FIELD, false, true, false>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
-        else tile_body<T, false, true, FIELD, false, false, sizeof(T) == 8>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+        else tile_body<T, false, true, FIELD, false, false, true>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
     }
 }
 
@@ -433,28 +432,28 @@ long long tile_count(int nx, int ny, int steps)
 }
 
 // Time of a launch of `steps` steps on `tiles` tiles, in microseconds.  A
-// launch costs a, a tile with its CU to itself l per step (latency), and a CU
-// with several tiles m + c per step for each.  Fitted on MI355X to 40x20 to
-// 1024^2 meshes and 1 to 6 steps a launch (FP64 1024^2: 32.6, 27.1 and 29.8
-// us a step for 1, 2 and 3 steps a launch; 128^2 cavity: 7.4, 4.8, 4.1, 3.8,
-// 3.7 and 3.7 us for 1 to 6).
-static double tile_launch_us(bool f64, long long tiles, int steps, int n_cu)
+// launch costs 4.5, a tile with its CU to itself 2.9 per step (latency), and a CU
+// with several tiles 1.5 + 1.25 per step for each.  Fitted on MI355X to 40x20 to
+// 1024^2 meshes and 1 to 6 steps a launch (1024^2: 32.6, 27.1 and 29.8 us a step
+// for 1, 2 and 3 steps a launch; 128^2 cavity: 7.4, 4.8, 4.1, 3.8, 3.7 and 3.7
+// us for 1 to 6).
+static double tile_launch_us(long long tiles, int steps, int n_cu)
 {
-    const double a = f64 ? 4.5 : 3.0, l = f64 ? 2.9 : 2.4, m = f64 ? 1.5 : 0.86, c = f64 ? 1.25 : 0.92;
-    const double per_cu = (double)((tiles + n_cu - 1) / (n_cu > 0 ? n_cu : 1));
-    return a + std::max(l * steps, per_cu * (m + c * steps));
+    const int cu = n_cu > 0 ? n_cu : 1;
+    const double per_cu = (double)((tiles + cu - 1) / cu);
+    return 4.5 + std::max(2.9 * steps, per_cu * (1.5 + 1.25 * steps));
 }
 
 // Steps per launch that give the shortest time per step: more steps save
 // launches and passes over memory, but overlap the tiles more.  `tiles_of`:
 // tiles for a number of steps per launch.
 template <class F>
-static int best_steps(bool f64, int n_cu, F tiles_of)
+static int best_steps(int n_cu, F tiles_of)
 {
     int best = 1;
     double best_us = 1e300;
     for (int s = 1; s <= TILE_MAX_STEPS; ++s) {
-        const double us = tile_launch_us(f64, tiles_of(s), s, n_cu) / s;
+        const double us = tile_launch_us(tiles_of(s), s, n_cu) / s;
         if (us < best_us) {
             best_us = us;
             best = s;
@@ -518,17 +517,15 @@ static int launch_tile_t(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void
 int tile_steps(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t0, long long k0, int steps,
                hipStream_t st)
 {
-    if (ctx->cfg.dtype == DUGKS_F64) return launch_tile_t<double>(ctx, ctx->pd, fin, fout, force, t0, k0, steps, st);
-    return launch_tile_t<float>(ctx, ctx->pf, fin, fout, force, t0, k0, steps, st);
+    return launch_tile_t<double>(ctx, ctx->pd, fin, fout, force, t0, k0, steps, st);
 }
 
 // nsteps steps from f_a, as dugks_run; *which_out as there
 int tile_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0, int nsteps, hipStream_t st,
              int* which_out)
 {
-    const bool f64 = ctx->cfg.dtype == DUGKS_F64;
     const int nx = ctx->cfg.n[0], ny = ctx->cfg.n[1];
-    const int most = best_steps(f64, ctx->n_cu, [&](int s) { return tile_count(nx, ny, s); });
+    const int most = best_steps(ctx->n_cu, [&](int s) { return tile_count(nx, ny, s); });
     void* cur = f_a;
     void* nxt = f_b;
     long long k = 0;
@@ -543,34 +540,24 @@ int tile_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0,
 }
 
 // steps per launch of a batch of n instances of nx[i] x ny[i] cells
-int tile_batch_steps(int dtype, int n, const int* nx, const int* ny, int n_cu)
+int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu)
 {
-    return best_steps(dtype == DUGKS_F64, n_cu, [&](int s) {
+    return best_steps(n_cu, [&](int s) {
         long long t = 0;
         for (int i = 0; i < n; ++i) t += tile_count(nx[i], ny[i], s);
         return t;
     });
 }
 
-template <typename T>
-static void tile_batch_t(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
-                         const void* forces, void* fout, const long long* step0, int step, int steps, hipStream_t st)
-{
-    auto kern = forces ? k_tile_batch<T, true> : k_tile_batch<T, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(TILE_NT), 0, st, (const Inst<T>*)insts, blocks,
-                       (const T*)fin, (const T*)forces, (T*)fout, step0, step, steps);
-}
-
 // `steps` steps of every instance; blocks: the nblocks workgroups of a launch of
 // `steps` steps
-hipError_t tile_batch_launch(int dtype, const void* insts, const TileBlock* blocks, long long nblocks,
-                             const void* fin, const void* forces, void* fout, const long long* step0, int step,
-                             int steps, hipStream_t st)
+hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
+                             const void* forces, void* fout, const long long* step0, int step, int steps,
+                             hipStream_t st)
 {
-    if (dtype == DUGKS_F64)
-        tile_batch_t<double>(insts, blocks, nblocks, fin, forces, fout, step0, step, steps, st);
-    else
-        tile_batch_t<float>(insts, blocks, nblocks, fin, forces, fout, step0, step, steps, st);
+    auto kern = forces ? k_tile_batch<double, true> : k_tile_batch<double, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(TILE_NT), 0, st, (const Inst<double>*)insts, blocks,
+                       (const double*)fin, (const double*)forces, (double*)fout, step0, step, steps);
     return hipGetLastError();
 }
 

@@ -86,13 +86,13 @@ inline int launch_chunk(int fixed, long long tiles, int nM, long long slots)
 // maximum keeps the compiler from trading instruction-level parallelism for
 // an occupancy the LDS never allows.  D3Q19 one lane per column: FP64 155 KB
 // -> one 4-wave workgroup per CU, FP32 78 KB -> two; two lanes per column
-// (512 threads): FP64 two waves per SIMD, FP32 up to four.  D2Q9 tiles are
+// (512 threads): FP32 up to four.  D2Q9 tiles are
 // small: up to 8.
 template <class LAT, typename T, bool SPLIT>
 __host__ __device__ constexpr int max_waves_per_eu()
 {
     if (LAT::D == 2) return 8;
-    if (SPLIT) return sizeof(T) == 8 ? 2 : 4;
+    if (SPLIT) return 4;
     return sizeof(T) == 8 ? 1 : 2;
 }
 

@@ -1,5 +1,5 @@
 // wave.hpp -- register exchange between the lanes of a wavefront, and the
-// per-cell stages of the D2Q9 step with every rounding written out.
+// per-cell stages of the steps with every rounding written out.
 //
 // The stages are used by several kernels that must give the same bits for
 // the same cell whatever tile, chunk or batch it is computed in, and with or
@@ -36,6 +36,125 @@ template <typename T>
 __device__ __forceinline__ T lane_next(T v) { return lane_dpp<DPP_NEXT>(v); }
 template <typename T>
 __device__ __forceinline__ T lane_prev(T v) { return lane_dpp<DPP_PREV>(v); }
+
+// value of the partner lane (same column, other half): v_permlane32_swap
+// exchanges lanes 32..63 of its first operand with lanes 0..31 of its second;
+// with both operands = v the partner's value is the second result in the
+// lower half-wave and the first in the upper one.  Both lanes of a pair are
+// always active together.
+__device__ __forceinline__ unsigned partner_u32(unsigned v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return __lane_id() < 32 ? r[1] : r[0];
+}
+__device__ __forceinline__ float partner(float v)
+{
+    return __builtin_bit_cast(float, partner_u32(__builtin_bit_cast(unsigned, v)));
+}
+__device__ __forceinline__ double partner(double v)
+{
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = partner_u32((unsigned)b), hi = partner_u32((unsigned)(b >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Lane-pair sums of two values at once: v_permlane32_swap(a, b) leaves
+// (a(l), b(l-32)) in its first result and (a(l+32), b(l)) in its second, so
+// one add gives the pair sum of a in the lower half-wave and that of b in
+// the upper one; a second swap of that sum with a copy of itself hands both
+// halves to every lane.  Each sum is the lower lane's value plus the upper
+// one's, bitwise what both lanes get from v + partner(v).  The copy is made
+// opaque to the compiler so that the swap never sees two equal operands.
+__device__ __forceinline__ void pair_sum2_u32(unsigned a, unsigned b, unsigned& r0, unsigned& r1)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    r0 = r[0];
+    r1 = r[1];
+}
+// M: how the pair is combined: 0 both sums plain; 1 a plain, b signed (the
+// lane's sign sg, +1 in the lower and -1 in the upper half-wave); 2 both
+// signed.  A signed sum is that of sg * x: the lower lane's value minus the
+// upper one's, bitwise what sg * x + partner(sg * x) gives, since
+// multiplying by -1 is exact.
+template <int M>
+__device__ __forceinline__ float pair_combine(float x0, float x1, float sg)
+{
+    if constexpr (M == 0) return x0 + x1;
+    else if constexpr (M == 1) return __builtin_fmaf(sg, x1, x0);
+    else return x0 - x1;
+}
+template <int M>
+__device__ __forceinline__ double pair_combine(double x0, double x1, double sg)
+{
+    if constexpr (M == 0) return x0 + x1;
+    else if constexpr (M == 1) return __builtin_fma(sg, x1, x0);
+    else return x0 - x1;
+}
+template <int M = 0>
+__device__ __forceinline__ void pair_sum2(float a, float b, float& sa, float& sb, float sg = 1.0f)
+{
+    unsigned x0, x1;
+    pair_sum2_u32(__float_as_uint(a), __float_as_uint(b), x0, x1);
+    const float sum = pair_combine<M>(__uint_as_float(x0), __uint_as_float(x1), sg);
+    unsigned c = __float_as_uint(sum);
+    asm volatile("" : "+v"(c));
+    unsigned y0, y1;
+    pair_sum2_u32(__float_as_uint(sum), c, y0, y1);
+    sa = __uint_as_float(y0);
+    sb = __uint_as_float(y1);
+}
+template <int M = 0>
+__device__ __forceinline__ void pair_sum2(double a, double b, double& sa, double& sb, double sg = 1.0)
+{
+    const unsigned long long ua = (unsigned long long)__double_as_longlong(a);
+    const unsigned long long ub = (unsigned long long)__double_as_longlong(b);
+    unsigned l0, l1, h0, h1;
+    pair_sum2_u32((unsigned)ua, (unsigned)ub, l0, l1);
+    pair_sum2_u32((unsigned)(ua >> 32), (unsigned)(ub >> 32), h0, h1);
+    const double sum = pair_combine<M>(__longlong_as_double((long long)(((unsigned long long)h0 << 32) | l0)),
+                                       __longlong_as_double((long long)(((unsigned long long)h1 << 32) | l1)), sg);
+    const unsigned long long us = (unsigned long long)__double_as_longlong(sum);
+    unsigned clo = (unsigned)us, chi = (unsigned)(us >> 32);
+    asm volatile("" : "+v"(clo), "+v"(chi));
+    pair_sum2_u32((unsigned)us, clo, l0, l1);
+    pair_sum2_u32((unsigned)(us >> 32), chi, h0, h1);
+    sa = __longlong_as_double((long long)(((unsigned long long)h0 << 32) | l0));
+    sb = __longlong_as_double((long long)(((unsigned long long)h1 << 32) | l1));
+}
+// the moments of a column from the two lanes' partial sums: rho = rh + rh
+// of the partner lane, j[a] = the pair sum of sg * sj[a]
+template <int D, typename T>
+__device__ __forceinline__ void moment_sums(T rh, const T (&sj)[3], T sg, T& rho, T (&j)[3])
+{
+    pair_sum2<1>(rh, sj[0], rho, j[0], sg);
+    if constexpr (D == 3) {
+        pair_sum2<2>(sj[1], sj[2], j[1], j[2], sg);
+    } else {
+        const T x = sg * sj[1];
+        j[1] = x + partner(x);
+    }
+}
+
+// value of lane l + N (N > 0) or l - N (N < 0) of the lane's 16-lane row
+// (DPP row shift; 0 where the source is outside the row)
+template <int N>
+__device__ __forceinline__ unsigned row_shift_u32(unsigned v)
+{
+    constexpr int ctrl = N > 0 ? 0x100 + N : 0x110 - N;  // row_shl:N / row_shr:-N
+    return (unsigned)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xf, 0xf, true);
+}
+template <int N>
+__device__ __forceinline__ float row_shift(float v)
+{
+    return __uint_as_float(row_shift_u32<N>(__float_as_uint(v)));
+}
+template <int N>
+__device__ __forceinline__ double row_shift(double v)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = row_shift_u32<N>((unsigned)b), hi = row_shift_u32<N>((unsigned)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
