@@ -17,9 +17,9 @@
 //   pass C (per cell): phi_hat += cp_t(s-t) d_hat_t(s-t) + cm_t(s+t) d_hat_t(s+t);
 //     reverse of Eq. (f_bar_+) and of the macroscopic recovery -> lam_n and
 //     the force-field gradient (cell term at t_n, face terms at t_n + h).
-// For the 2-D sets passes B and C run as one launch over cell tiles whose
-// d_hat (halo included) is formed in LDS, so a step reads and writes main
-// memory in three passes (phi, faces, cells) instead of four.
+// For the 2-D set in FP32 passes B and C run as one launch over cell tiles whose
+// d_hat (halo included) is formed in LDS, and so do f-bar-plus and pass A; in
+// FP64 it takes one launch for everything (adjoint_tile.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -66,6 +66,10 @@ __device__ __forceinline__ Partials<LAT, T> partials(int q, T rho, const T* u, c
     }
     return r;
 }
+
+// adjoint_tile.hip: one step of D2Q9 in FP64
+void adjoint_tile_launch(const Inst<double>* Pd, const Inst<double>& P, const void* f, const void* force, double gt,
+                         double gth, const void* lam, void* lam_out, void* grad, hipStream_t st);
 
 template <typename T>
 __device__ __forceinline__ int wrapc(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
@@ -1232,19 +1236,46 @@ static int adjoint_scratch(dugks_ctx* ctx, size_t need, bool stat, void** out)
     return DUGKS_OK;
 }
 
+// scratch of the passes below: on a fully periodic mesh, and with walls
+template <class LAT, typename T>
+static size_t adjoint_bytes(const Inst<T>& P)
+{
+    constexpr int Q = LAT::Q, D = LAT::D;
+    const size_t es = sizeof(T);
+    return (size_t)D * Q * P.nc * es                          // face adjoints
+           + (size_t)D * D * P.nc * es                        // face force adjoints
+           + (D == 2 ? 0 : (size_t)P.ne * Q * es)             // phi (extended)
+           + (D == 2 ? 0 : (size_t)Q * P.nc * es)             // phi_hat partial
+           + (D == 2 ? 0 : (size_t)D * Q * P.nc * es);        // d_hat
+}
+template <class LAT, typename T>
+static size_t adjoint_walls_bytes(const Inst<T>& P)
+{
+    constexpr int Q = LAT::Q, D = LAT::D;
+    const size_t es = sizeof(T);
+    size_t nfaces = 0, nwall = 0;  // nwall: 2 sides x lines of each wall axis
+    for (int a = 0; a < D; ++a) {
+        nfaces += (size_t)face_total(P, a);
+        if (!P.per[a]) nwall += (size_t)(2 * (P.nc / P.n[a]));
+    }
+    return (size_t)P.ne * Q * es          // phi (extended)
+           + nfaces * Q * es              // face adjoints
+           + nfaces * D * es              // face-force adjoints
+           + nwall * (Q + D) * es         // NEQ parts of the opposite interfaces
+           + (size_t)P.ne * Q * es        // phi_hat (extended)
+           + (size_t)D * P.ne * Q * es    // d_hat (extended)
+           + (size_t)P.ne * D * es        // force adjoint (extended)
+           + (size_t)P.nc * (Q + D) * es; // phi_hat and force adjoint gathered per cell
+}
+
 template <class LAT, typename T>
 static int adjoint_step(dugks_ctx* ctx, const Inst<T>& P, const void* fn, const void* force, double t,
                         const void* lam_np1, void* lam_n, void* grad_force, hipStream_t st, bool stat)
 {
     constexpr int Q = LAT::Q, D = LAT::D;
-    const size_t es = sizeof(T);
     // 2-D sets: two tiled launches (f-bar-plus with pass A, passes B with C)
     constexpr bool tiled = D == 2;
-    const size_t need = (size_t)D * Q * P.nc * es            // face adjoints
-                        + (size_t)D * D * P.nc * es          // face force adjoints
-                        + (tiled ? 0 : (size_t)P.ne * Q * es)        // phi (extended)
-                        + (tiled ? 0 : (size_t)Q * P.nc * es)        // phi_hat partial
-                        + (tiled ? 0 : (size_t)D * Q * P.nc * es);   // d_hat
+    const size_t need = adjoint_bytes<LAT, T>(P);
     void* work = nullptr;
     const int src = adjoint_scratch(ctx, need, stat, &work);
     if (src != DUGKS_OK) return src;
@@ -1282,20 +1313,7 @@ static int adjoint_step_walls(dugks_ctx* ctx, const Inst<T>& P, const void* fn, 
                               const void* lam_np1, void* lam_n, void* grad_force, hipStream_t st, bool stat)
 {
     constexpr int Q = LAT::Q, D = LAT::D;
-    const size_t es = sizeof(T);
-    size_t nfaces = 0;
-    for (int a = 0; a < D; ++a) nfaces += (size_t)face_total(P, a);
-    size_t nwall = 0;  // 2 sides x lines of each wall axis
-    for (int a = 0; a < D; ++a)
-        if (!P.per[a]) nwall += (size_t)(2 * (P.nc / P.n[a]));
-    const size_t need = (size_t)P.ne * Q * es        // phi (extended)
-                        + nfaces * Q * es            // face adjoints
-                        + nfaces * D * es            // face-force adjoints
-                        + nwall * (Q + D) * es       // NEQ parts of the opposite interfaces
-                        + (size_t)P.ne * Q * es      // phi_hat (extended)
-                        + (size_t)D * P.ne * Q * es  // d_hat (extended)
-                        + (size_t)P.ne * D * es      // force adjoint (extended)
-                        + (size_t)P.nc * (Q + D) * es; // phi_hat and force adjoint gathered per cell
+    const size_t need = adjoint_walls_bytes<LAT, T>(P);
     void* work = nullptr;
     const int src = adjoint_scratch(ctx, need, stat, &work);
     if (src != DUGKS_OK) return src;
@@ -1399,26 +1417,37 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
     for (int s = 0; s < 2 * ctx->D; ++s)
         if (ctx->cfg.bc[s] != DUGKS_PERIODIC) periodic = false;
     const hipStream_t st = (hipStream_t)stream;
+    const char* env = getenv("DUGKS_ADJOINT_GENERAL");
+    const bool general = env && env[0] == '1';
+    const bool d2 = ctx->cfg.lattice == DUGKS_D2Q9, f64 = ctx->cfg.dtype == DUGKS_F64;
+    // D2Q9 in FP64: one launch on tiles, no scratch; the allocation-free entry
+    // point keeps the sizes it takes.  FP32 stays on the passes below: its
+    // rounding is part of what callers compare.
+    if (d2 && f64 && !general) {
+        if (stat) {
+            void* unused = nullptr;
+            const int rc = adjoint_scratch(ctx, periodic ? adjoint_bytes<D2Q9, double>(ctx->pd)
+                                                         : adjoint_walls_bytes<D2Q9, double>(ctx->pd), true, &unused);
+            if (rc != DUGKS_OK) return rc;
+        }
+        adjoint_tile_launch((const Inst<double>*)ctx->inst_dev, ctx->pd, f_n, force, tfac(ctx->pd, t_n),
+                            tfac(ctx->pd, t_n + 0.5 * (double)ctx->cfg.dt), lam_np1, lam_n, grad_force, st);
+        return hip_check(ctx, hipGetLastError(), "adjoint launch");
+    }
     // meshes with walls: the general reverse pass (also taken on periodic
     // meshes when DUGKS_ADJOINT_GENERAL=1, to cross-check it)
-    const char* gen = getenv("DUGKS_ADJOINT_GENERAL");
-    if (!periodic || (gen && gen[0] == '1')) {
-        if (ctx->cfg.lattice == DUGKS_D2Q9) {
-            if (ctx->cfg.dtype == DUGKS_F64)
+    if (!periodic || general) {
+        if (d2) {
+            if (f64)
                 return adjoint_step_walls<D2Q9, double>(ctx, ctx->pd, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
             return adjoint_step_walls<D2Q9, float>(ctx, ctx->pf, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
         }
-        if (ctx->cfg.dtype == DUGKS_F64)
+        if (f64)
             return adjoint_step_walls<D3Q19, double>(ctx, ctx->pd, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
         return adjoint_step_walls<D3Q19, float>(ctx, ctx->pf, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
     }
-    if (ctx->cfg.lattice == DUGKS_D2Q9) {
-        if (ctx->cfg.dtype == DUGKS_F64)
-            return adjoint_step<D2Q9, double>(ctx, ctx->pd, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
-        return adjoint_step<D2Q9, float>(ctx, ctx->pf, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
-    }
-    if (ctx->cfg.dtype == DUGKS_F64)
-        return adjoint_step<D3Q19, double>(ctx, ctx->pd, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
+    if (d2) return adjoint_step<D2Q9, float>(ctx, ctx->pf, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
+    if (f64) return adjoint_step<D3Q19, double>(ctx, ctx->pd, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
     return adjoint_step<D3Q19, float>(ctx, ctx->pf, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
 }
 }  // namespace dugks

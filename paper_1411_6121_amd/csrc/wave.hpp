@@ -318,7 +318,7 @@ __device__ __forceinline__ void d2_wall(const Inst<T>& P, int s, int into, T (&v
             const T eu = A == 0 ? fma_(T(t), P.uw[s][1], T(into) * P.uw[s][0])
                                 : fma_(T(t), P.uw[s][0], T(into) * P.uw[s][1]);
             const T w = t == 0 ? d2_w<T>(1) : d2_w<T>(0);
-            const T src = into > 0 ? v[d2_q(A, -1, 2 - k)] : v[d2_q(A, 1, 2 - k)];
+            const T vm = v[d2_q(A, -1, 2 - k)], vp = v[d2_q(A, 1, 2 - k)], src = into > 0 ? vm : vp;
             nv[k] = fma_(T(2) * P.eqB * w, eu, src);
         }
 #pragma unroll
