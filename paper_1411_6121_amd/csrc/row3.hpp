@@ -324,16 +324,6 @@ __device__ __forceinline__ void row_body(const Inst<T>& P, const T* __restrict__
         for (int k = 0; k < K; ++k) f[k] = fp[k * qstep];
         r = fin[rcol + o];
     };
-    auto ghost1 = [&](T& a) {
-        if (xlo) {
-            const T s1 = row_next(a), s2 = row_next(s1);
-            if (glo) a = fma_(rxl, s2 - s1, s1);
-        }
-        if (xhi) {
-            const T s1 = row_prev(a), s2 = row_prev(s1);
-            if (ghi) a = fma_(rxh, s2 - s1, s1);
-        }
-    };
     // f-bar-plus (Eq. f_bar_+) of a loaded plane, ghost columns included
     auto make_phi = [&](const T (&f)[K], T r, T (&g)[3], T (&phi)[K], T& pr) {
         T G[3] = {T(0), T(0), T(0)};
@@ -347,13 +337,30 @@ __device__ __forceinline__ void row_body(const Inst<T>& P, const T* __restrict__
         const T fe = T(LAT::w(LAT::REST)) * E.a;
         pr = fma_(P.B1, fe - r, r);
         if constexpr (ACC) pr = fma_(P.C1 * (T(0) - E.g), fe, pr);
-        if (xlo || xhi) {
+        if (xlo) {
+            auto ghost = [&](T& a) {
+                const T s1 = row_next(a), s2 = row_next(s1), v = fma_(rxl, s2 - s1, s1);
+                a = glo ? v : a;
+            };
 #pragma unroll
-            for (int k = 0; k < K; ++k) ghost1(phi[k]);
-            ghost1(pr);
+            for (int k = 0; k < K; ++k) ghost(phi[k]);
+            ghost(pr);
             if constexpr (FIELD) {
 #pragma unroll
-                for (int d = 0; d < 3; ++d) ghost1(g[d]);
+                for (int d = 0; d < 3; ++d) ghost(g[d]);
+            }
+        }
+        if (xhi) {
+            auto ghost = [&](T& a) {
+                const T s1 = row_prev(a), s2 = row_prev(s1), v = fma_(rxh, s2 - s1, s1);
+                a = ghi ? v : a;
+            };
+#pragma unroll
+            for (int k = 0; k < K; ++k) ghost(phi[k]);
+            ghost(pr);
+            if constexpr (FIELD) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) ghost(g[d]);
             }
         }
     };
