@@ -241,17 +241,20 @@ int dugks_velocity_change(dugks_ctx* ctx, const void* f_a, const void* f_b, cons
  * or tanh-stretched axes:
  *   lam_n       = (d f_{n+1} / d f_n)^T lam_np1
  *   grad_force += (d f_{n+1} / d G^)^T lam_np1   (nullable, [D])
- * The forward intermediates are recomputed from f_n (no tape).  D2Q9 in
- * FP64 takes one launch over cell tiles on any boundary set and no scratch.
- * Otherwise fully periodic meshes take a gather form: in 2-D two launches
- * over cell tiles (f-bar-plus and the interface adjoints; then the cell
- * adjoints, the neighbours' terms staged in LDS), in 3-D four passes; meshes
- * with walls a gather form over every face and the ghost-extended grid (the
- * ghost rule of the ghost values is transposed).  Their scratch (2-D
- * periodic: D (Q + D) values per cell; otherwise about (2 + D) Q values per
- * extended cell plus (Q + D) per face and per cell) is allocated on first use
- * and kept by the context.  lam_n must not alias f_n or lam_np1.  The
- * original-model variant and D3Q27 return DUGKS_EUNSUPPORTED.  Asynchronous.
+ * The forward intermediates are recomputed from f_n (no tape).  In FP64
+ * D2Q9 takes one launch over cell tiles and no scratch, D3Q19 three launches
+ * (f-bar-plus, faces, cells; wall axes of at least four cells, up to about
+ * 28 million cells) with 4 Q + 9 values of scratch per cell.  Otherwise fully
+ * periodic meshes take a gather form: in 2-D two launches over cell tiles
+ * (f-bar-plus and the interface adjoints; then the cell adjoints, the
+ * neighbours' terms staged in LDS), in 3-D four passes; meshes with walls a
+ * gather form over every face and the ghost-extended grid (the ghost rule of
+ * the ghost values is transposed), whose scratch (2-D periodic: D (Q + D)
+ * values per cell; otherwise about (2 + D) Q values per extended cell plus
+ * (Q + D) per face and per cell) also bounds what the allocation-free entry
+ * point below takes.  Scratch is allocated on first use and kept by the
+ * context.  lam_n must not alias f_n or lam_np1.  The original-model variant
+ * and D3Q27 return DUGKS_EUNSUPPORTED.  Asynchronous.
  */
 int dugks_step_adjoint(dugks_ctx* ctx, const void* f_n, const void* force, double t_n,
                        const void* lam_np1, void* lam_n, void* grad_force, void* stream);
@@ -265,8 +268,8 @@ int dugks_step_adjoint(dugks_ctx* ctx, const void* f_n, const void* force, doubl
  * allocated buffer.  The call allocates and frees nothing.  The caller still
  * owns every input and output.  A problem whose scratch exceeds 64 MiB is
  * rejected with DUGKS_EINVAL (the message states both sizes; 64 MiB holds
- * the 256^2 D2Q9 FP64 adjoint, periodic or with walls), and so is a D2Q9
- * FP64 problem beyond that size, though it takes no scratch.  The current device
+ * the 256^2 D2Q9 FP64 adjoint, periodic or with walls); the sizes
+ * compared are those of the gather forms above, also where a launch needs less.  The current device
  * must be the one the context was created on.  Every call on one GPU
  * shares that GPU's area and every element the kernels read is written
  * earlier in the same call, so nothing needs clearing; calls that overlap

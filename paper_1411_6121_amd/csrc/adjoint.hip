@@ -17,7 +17,8 @@
 //   pass C (per cell): phi_hat += cp_t(s-t) d_hat_t(s-t) + cm_t(s+t) d_hat_t(s+t);
 //     reverse of Eq. (f_bar_+) and of the macroscopic recovery -> lam_n and
 //     the force-field gradient (cell term at t_n, face terms at t_n + h).
-// For the 2-D set in FP32 passes B and C run as one launch over cell tiles whose
+// D3Q19 in FP64 has passes of its own (adjoint_cells.hip), these serving it where
+// those do not fit.  For the 2-D set in FP32 passes B and C run as one launch over cell tiles whose
 // d_hat (halo included) is formed in LDS, and so do f-bar-plus and pass A; in
 // FP64 it takes one launch for everything (adjoint_tile.hip).
 #include <hip/hip_runtime.h>
@@ -70,6 +71,13 @@ __device__ __forceinline__ Partials<LAT, T> partials(int q, T rho, const T* u, c
 // adjoint_tile.hip: one step of D2Q9 in FP64
 void adjoint_tile_launch(const Inst<double>* Pd, const Inst<double>& P, const void* f, const void* force, double gt,
                          double gth, const void* lam, void* lam_out, void* grad, hipStream_t st);
+
+// adjoint_cells.hip: one step of D3Q19 in FP64; the meshes it takes, the scratch
+// it needs
+bool adjoint_cells_fit(const Inst<double>& P);
+size_t adjoint_cells_bytes(const Inst<double>& P);
+void adjoint_cells_launch(const Inst<double>* Pd, const Inst<double>& P, void* work, const void* f, const void* force,
+                          double gt, double gth, const void* lam, void* lam_out, void* grad, hipStream_t st);
 
 template <typename T>
 __device__ __forceinline__ int wrapc(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
@@ -1432,6 +1440,19 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
         }
         adjoint_tile_launch((const Inst<double>*)ctx->inst_dev, ctx->pd, f_n, force, tfac(ctx->pd, t_n),
                             tfac(ctx->pd, t_n + 0.5 * (double)ctx->cfg.dt), lam_np1, lam_n, grad_force, st);
+        return hip_check(ctx, hipGetLastError(), "adjoint launch");
+    }
+    // D3Q19 in FP64: three launches over the cells, with less scratch than the
+    // passes below (the allocation-free entry point keeps the sizes it takes)
+    if (!d2 && f64 && !general && adjoint_cells_fit(ctx->pd)) {
+        const size_t need = !stat      ? adjoint_cells_bytes(ctx->pd)
+                            : periodic ? adjoint_bytes<D3Q19, double>(ctx->pd)
+                                       : adjoint_walls_bytes<D3Q19, double>(ctx->pd);
+        void* work = nullptr;
+        const int rc = adjoint_scratch(ctx, need, stat, &work);
+        if (rc != DUGKS_OK) return rc;
+        adjoint_cells_launch((const Inst<double>*)ctx->inst_dev, ctx->pd, work, f_n, force, tfac(ctx->pd, t_n),
+                             tfac(ctx->pd, t_n + 0.5 * (double)ctx->cfg.dt), lam_np1, lam_n, grad_force, st);
         return hip_check(ctx, hipGetLastError(), "adjoint launch");
     }
     // meshes with walls: the general reverse pass (also taken on periodic
