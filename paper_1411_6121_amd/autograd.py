@@ -13,8 +13,8 @@ import math
 
 import torch
 
-from . import (dugks_destroy, dugks_init, dugks_init_vjp, dugks_moments, dugks_moments_vjp, dugks_reset,
-               dugks_step, dugks_step_adjoint, shape_of, torch_dtype)
+from . import (_VP, _check, _ptr, _stream, dugks_destroy, dugks_init, dugks_init_vjp, dugks_moments,
+               dugks_moments_vjp, dugks_run, dugks_step, load, shape_of)
 
 
 class _Rollout(torch.autograd.Function):
@@ -23,14 +23,22 @@ class _Rollout(torch.autograd.Function):
         Q, D, shp = shape_of(cfg)
         dt = float(cfg["dt"])
         f = torch.empty((Q,) + shp, dtype=force.dtype, device=force.device)
-        g = torch.empty_like(f)
         h = dugks_init(cfg, f, None, u0, force)
-        ckpt = {0: f.clone()}
-        for n in range(nsteps):
+        # a segment at a time, out of place from its checkpoint; two calls each
+        # (a call per step costs the host more than a step takes on the device)
+        ckpt = {0: f}
+        spare = torch.empty_like(f)
+        n = 0
+        while n < nsteps:
+            m = min(abs(seg), nsteps - n)
+            g = torch.empty_like(f)
             dugks_step(h, f, g, force, n * dt)
-            f, g = g, f
-            if (n + 1) % seg == 0 and (n + 1) < nsteps:
-                ckpt[n + 1] = f.clone()
+            if m > 1 and dugks_run(h, g, spare, m - 1, force, (n + 1) * dt):
+                g, spare = spare, g
+            f = g
+            n += m
+            if n < nsteps:
+                ckpt[n] = f
         u = torch.empty((D,) + shp, dtype=force.dtype, device=force.device)
         dugks_moments(h, f, force, nsteps * dt, None, u, None, totals=False)
         actx.h, actx.cfg, actx.nsteps, actx.seg, actx.ckpt = h, cfg, nsteps, seg, ckpt
@@ -52,16 +60,29 @@ class _Rollout(torch.autograd.Function):
         # one segment's states, recomputed step by step straight into their
         # slots (slot 0 is the checkpoint itself)
         seg_states = torch.empty((seg - 1, Q) + shp, dtype=force.dtype, device=force.device) if seg > 1 else None
+        # the library's entry points with their arguments converted once: through
+        # the checked wrappers a call took the host 9 to 11 us, longer than the
+        # device takes for a small mesh's step
+        lib = load()
+        step, adjoint, hp, st = lib.dugks_step, lib.dugks_step_adjoint, _VP(h), _stream(None)
+        fp, gp = _ptr(force), _ptr(gforce)
+        slots, nbytes = seg_states.data_ptr() if seg > 1 else 0, lam.numel() * lam.element_size()
+
+        def call(fn, *args):
+            rc = fn(*args)
+            if rc:
+                _check(rc, hp)
+
         for s0 in reversed(starts):
             s1 = min(s0 + seg, nsteps)
 
             def state(n):
-                return ckpt[s0] if n == s0 else seg_states[n - s0 - 1]
+                return ckpt[s0].data_ptr() if n == s0 else slots + (n - s0 - 1) * nbytes
 
             for n in range(s0, s1 - 1):
-                dugks_step(h, state(n), state(n + 1), force, n * dt)
+                call(step, hp, state(n), state(n + 1), fp, n * dt, st)
             for n in reversed(range(s0, s1)):
-                dugks_step_adjoint(h, state(n), lam, lam2, force, n * dt, gforce)
+                call(adjoint, hp, state(n), fp, n * dt, lam.data_ptr(), lam2.data_ptr(), gp, st)
                 lam, lam2 = lam2, lam
         gu0 = torch.zeros_like(u0)
         dugks_init_vjp(h, lam, u0, force, 0.0, gu0, gforce)
