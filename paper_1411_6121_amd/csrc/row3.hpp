@@ -713,22 +713,26 @@ struct RowShape {
     __attribute__((amdgpu_flat_work_group_size(RowShape<LAT, T>::NT, RowShape<LAT, T>::NT), \
                    amdgpu_waves_per_eu(RowShape<LAT, T>::WPE)))
 
-// Planes marched per workgroup.  W = tiles x ceil(n / c) workgroups run on S
-// resident ones in about W / S + 0.6 rounds (at least one) of c + 1 arrivals
-// (the two that prime a march are worth about one).  The chunk minimises their
-// product, the larger one on ties.  Measured (us a step for c = 4, 8, 16):
-// 128^3 periodic FP64 302, 275, 267; 120x101x90 stretched FP64 227, 241, 243
-// (32: 287); 96x64x75 with a field FP64 97, 109, 134; D3Q27 75x66x50 140, 143,
-// 262.
+// Planes marched per workgroup.  x = tiles x ceil(n / c) / S rounds of
+// workgroups on S resident ones; the last round is full or not, so their
+// number is taken as the mean of x + 0.8 and of ceil(x), each of c + 0.9
+// arrivals (the two that prime a march are worth about one).  The chunk of 1, 2,
+// 3, 4, 6, 8, .. 32 planes that minimises the product, the larger one on
+// ties.  Measured (us a step for c = 2, 3, 4, 6, 8): 128^3 cavity 415, 378, 355,
+// 353, 337 (16: 355); 120 x 101 x 90 cavity 240, 222, 216, 208, 225; 96 x 64 x 75
+// with a field 112, 103, 105, 107, 118; 40 x 90 x 30 49, 42, 52, 62, 76; 48 x 40 x
+// 36 41, 51, 52, 69, 87; D3Q27 75 x 66 x 50 127, 121, 126, 131, 144.  Over
+// sixteen such meshes its choice is within 2 % of the best but for two (7, 10 %).
 inline int row_chunk(long long tiles, int nz, long long slots)
 {
     slots = slots > 1 ? slots : 1;
     int best = 1;
     double best_cost = 1e300;
-    for (int c = 1; c <= 32; c *= 2) {
+    for (int c : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
         const int cc = c < nz ? c : nz;
-        const double rounds = (double)(tiles * ((nz + cc - 1) / cc)) / (double)slots + 0.6;
-        const double cost = (rounds > 1.0 ? rounds : 1.0) * (cc + 1.0);
+        const long long wgs = tiles * ((nz + cc - 1) / cc);
+        const double rounds = 0.5 * ((double)wgs / (double)slots + 0.8) + 0.5 * (double)((wgs + slots - 1) / slots);
+        const double cost = rounds * (cc + 0.9);
         if (cost <= best_cost) {
             best_cost = cost;
             best = cc;
@@ -751,8 +755,15 @@ __global__ ROW_BOUNDS(LAT, T) void k_row(const Inst<T>* __restrict__ Pp, const T
         gt = tfac_dev(P, t);
         gth = tfac_dev(P, t + 0.5 * P.dtd);
     }
-    const int b = xcd_order((int)blockIdx.x, (int)gridDim.x);
-    const int tile = b % tiles, ck = b / tiles;
+    // the chunks at the z walls first, then the others, each part in XCD order:
+    // they take up to twice as long, and with all chunks in one order the first
+    // and the last XCD had nothing else (128^3 cavity 368 -> 336 us a step; bands
+    // of tiles with all their chunks per XCD: 355, but then the y walls sit on
+    // two XCDs, D3Q27 136 -> 150)
+    const int nck = (P.n[2] + chunk - 1) / chunk, nb = (int)gridDim.x, wz = P.per[2] || nck < 3 ? 0 : 2 * tiles;
+    const bool zw = (int)blockIdx.x < wz;
+    const int b = zw ? xcd_order((int)blockIdx.x, wz) : xcd_order((int)blockIdx.x - wz, nb - wz);
+    const int tile = b % tiles, ck = zw ? (b < tiles ? 0 : nck - 1) : b / tiles + (wz ? 1 : 0);
     if (row_no_wall(P, BY, tiles0, tile, ck, chunk))
         row_body<LAT, T, BY, UNI, ACC, FIELD, ORIG, true>(P, fin, force, fout, gt, gth, chunk, tiles0, tile, ck, lds);
     else
