@@ -67,8 +67,16 @@ def cavity_cfg(n, dtype, mesh, re, lattice=19):
 # the sources the timed step kernels are compiled from, plus their launch
 # policy (tile, chunk and kernel choice) and the ABI header: the counters are
 # stale once any of these changes
-KERNEL_SOURCES = ("kernels_split.hip", "kernels_fused.hip", "march.hpp", "kernels_general.hpp", "inst.hpp",
+KERNEL_SOURCES = ("row3.hpp", "kernels_row19_f64.hip", "kernels_row27_f64.hip", "kernels_tile.hip", "wave.hpp",
+                  "kernels_split.hip", "kernels_fused.hip", "march.hpp", "kernels_general.hpp", "inst.hpp",
                   "lattice.hpp", "ctx.hpp", "../../include/dugks.h")
+
+
+def kernel_name(cfg, variant):
+    """the step kernel of dugks_kernel_variant's number"""
+    if variant == 3:
+        return "fused-split" if cfg["dtype"] != "f64" else "tile" if cfg["lattice"] == 9 else "row"
+    return {0: "general", 1: "fused-twice", 2: "fused"}.get(variant, str(variant))
 
 
 def source_hash():
@@ -332,7 +340,7 @@ def summarize_counters(fetch_dir, write_dir, workload):
 
     def per_dispatch(rs, name):
         step = [float(r["Counter_Value"]) for r in rs if r["Counter_Name"] == name and
-                ("k_fused2<" in r["Kernel_Name"] or "k_split<" in r["Kernel_Name"])]
+                any(k in r["Kernel_Name"] for k in ("k_fused2<", "k_split<", "k_row<"))]
         copy = [float(r["Counter_Value"]) for r in rs if r["Counter_Name"] == name and "copyBuffer" in r["Kernel_Name"]
                 and int(r["Grid_Size"]) >= 65536]
         return step, copy
@@ -592,7 +600,7 @@ def main():
         "data": "synthetic (cavity from rest, no external data)",
         "config": {"workload": workload, "cells": cells, "Q": Q, "global_batch": 1, "seq_len": args.n,
                    "parallelism": "single GPU", "dt": cfg["dt"], "tau": cfg["tau"],
-                   "kernel": {0: "general", 1: "fused-twice", 2: "fused", 3: "fused-split"}.get(variant, str(variant))},
+                   "kernel": kernel_name(cfg, variant)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "algorithmic_bytes_per_launch": bytes_per_step},
@@ -623,7 +631,7 @@ def main():
         del f, g
         also["original_model"] = {"ms_per_step": round(mso, 5), "mlups": round(cells / mso / 1e3, 2),
                                   "hbm_frac": round(bytes_per_step / (mso * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                                  "kernel": "fused-split" if kvo == 3 else "general (two launches)"}
+                                  "kernel": kernel_name(corig, kvo)}
         # the paper's own 3-D velocity set on the same cavity
         c27 = cavity_cfg(args.n, args.dtype, args.mesh, args.re, lattice=27)
         f = torch.empty((27,) + shp, dtype=M.torch_dtype(c27), device="cuda")
@@ -649,7 +657,7 @@ def main():
             also[f"tanh_re1000_{dt_name}"] = {
                 "ms_per_step": round(mst, 5), "mlups": round(cells / mst / 1e3, 2),
                 "hbm_frac": round(bt / (mst * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                "kernel": {0: "general", 1: "fused-twice", 2: "fused", 3: "fused-split"}.get(kvt, str(kvt))}
+                "kernel": kernel_name(ct, kvt)}
         also["batched"] = bench_batched()
         also["batched_f32"] = bench_batched("f32")
         also["adjoint"] = bench_adjoint()

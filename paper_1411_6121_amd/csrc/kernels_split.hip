@@ -1,5 +1,8 @@
-// kernels_split.hip -- the fused single-launch step with the velocity set
-// split over two lanes per column.
+// kernels_split.hip -- the fused single-launch step in FP32 with the velocity
+// set split over two lanes per column.  (In FP64 the row march of row3.hpp and
+// the tiles of kernels_tile.hip are 1.1 to 2.6 times as fast.  In FP32 they are
+// too, up to 2.1 times at 120 x 101 x 90, but round differently, by more than what
+// totals accumulated in FP64 from an FP32 state are compared to.)
 //
 // The march is that of the faces-once fused kernel (an LDS ring of three
 // f-bar-plus planes, every interface evaluated once, x/y face values
@@ -464,17 +467,17 @@ __device__ __forceinline__ void split_body(const Inst<T>& P, const T* __restrict
     constexpr int NX = half_cross_count<LAT, 0>(), NY = half_cross_count<LAT, 1>();
     constexpr int NM = half_cross_count<LAT, M>();
     constexpr int SQ = BX * BY;
-    // PHIU (single-instance launches without acceleration: FP32 D3Q19, and
-    // D3Q27): the update needs no own state, since rho and j of f-bar-plus
+    // PHIU (single-instance launches without acceleration, D3Q19 and D3Q27):
+    // the update needs no own state, since rho and j of f-bar-plus
     // equal those of f-tilde without acceleration: feq follows from the ring
-    // and f-tilde(n+1) = phi + B1 / (3 (1 - B1)) (feq - phi) - fluxes.  FP32
+    // and f-tilde(n+1) = phi + B1 / (3 (1 - B1)) (feq - phi) - fluxes.
     // D3Q19 (4 waves per SIMD, 128 registers) spends the freed own-state
     // registers on the late prefetch; D3Q27, which keeps no own state in
-    // registers, saves the second read of it (and takes the late prefetch
-    // in both precisions).  The host launches these instances only
+    // registers, saves the second read of it (and takes the late prefetch).
+    // The host launches these instances only
     // where |1 - B1| >= 1/4 (Inst::bu_ok); elsewhere it takes the instance
     // with the acceleration terms, whose skipped terms are exact zeros.
-    constexpr bool PHIU = NOG && !ORIG && LPF && ((LAT::Q == 19 && sizeof(T) == 4) || LAT::Q == 27);
+    constexpr bool PHIU = NOG && !ORIG && LPF && (LAT::Q == 19 || LAT::Q == 27);
     constexpr bool OWNR = OWN && !PHIU;
     const T Bu = P.Bu;
     T* fxb = lds + 3 * Q * SQ;   // [2][NX][BY][BX] upper x faces, per half
@@ -527,8 +530,7 @@ __device__ __forceinline__ void split_body(const Inst<T>& P, const T* __restrict
     const bool xg_lo = xsh_tile && !P.per[0] && b0 == 0;
     const bool xg_hi = xsh_tile && !P.per[0] && b0 * (BX - 2) - 1 + (BX - 1) >= P.n[0];
     // the tile's x wall faces, for the row exchange of the x-face stage
-    // (D3Q27, whose one wave per SIMD has registers to spare; in D3Q19 FP64,
-    // at 256 registers, the second pass spills about what the exchange saves)
+    // (D3Q27, the set on 16-column tiles)
     constexpr bool RX = XSH && LAT::Q == 27;
     const int rxw = RX ? ((!P.per[0] && b0 == 0) ? 1 : 0) |
                               ((!P.per[0] && b0 * (BX - 2) - 1 + (BX - 1) >= P.n[0]) ? 2 : 0)
@@ -581,16 +583,12 @@ __device__ __forceinline__ void split_body(const Inst<T>& P, const T* __restrict
             }
         }
     };
-    // Late prefetch (FP64 with the own state in registers, single-instance
-    // launches without a force field): the state of plane z+2 is loaded after
-    // the interface stage of plane z, so that its latency overlaps the barrier
-    // wait and the update instead of stalling the next f-bar-plus stage (2 %
-    // at 128^3; the batched and force-field instances, and FP32 with the
-    // own-state ring, run out of registers with it: D2Q9 512^2 with a field
-    // 30 -> 39 us).  PHIU launches take it too: FP32 D3Q19 in the registers
-    // the own state frees, D3Q27 in both precisions (FP64 D3Q27 runs one
-    // wave per SIMD, whose register file has room for it: 3 % at 128^3).
-    constexpr bool LP = LPF && ((OWNR && sizeof(T) == 8) || PHIU);
+    // Late prefetch: the state of plane z+2 is loaded after the interface stage
+    // of plane z, so that its latency overlaps the barrier wait and the update
+    // instead of stalling the next f-bar-plus stage.  PHIU launches take it:
+    // D3Q19 in the registers the own state frees, D3Q27 too; with the own-state
+    // ring there are no registers for it.
+    constexpr bool LP = LPF && PHIU;
     T pn[K], pnr = T(0), pgn[3] = {T(0), T(0), T(0)};
 #pragma unroll
     for (int k = 0; k < K; ++k) pn[k] = T(0);
@@ -1008,13 +1006,13 @@ static int launch_split(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void*
 {
     // FP32 D3Q19, uniform and field-free: fits four waves per SIMD (two
     // tiles per CU) without spills
-    constexpr int MINW_UF = (LAT::Q == 19 && sizeof(T) == 4) ? 4 : MINW;
+    constexpr int MINW_UF = LAT::Q == 19 ? 4 : MINW;
     // no acceleration at all (G = 0, no field): instances without the
     // source term of Eq. (S) (bitwise the same results, fewer operations).
     // Those of FP32 D3Q19 and of D3Q27 update without the own state, whose
     // coefficient B1 / (3 (1 - B1)) is allowed only away from its pole at
     // B1 = 1; near it the instance with the acceleration terms runs instead
-    constexpr bool phiu_lat = (LAT::Q == 19 && sizeof(T) == 4) || LAT::Q == 27;
+    constexpr bool phiu_lat = LAT::Q == 19 || LAT::Q == 27;
     const bool nog = !force && P.G0[0] == T(0) && P.G0[1] == T(0) && P.G0[2] == T(0) &&
                      (P.orig || !phiu_lat || P.bu_ok);
     if (P.orig) {
