@@ -25,9 +25,9 @@
 // then by L1 (a load of 64 doubles takes 17 tag lookups) and, beyond the 256 MB
 // cache, by memory (two of the three passes read or write 57 values a cell).
 // 48 x 40 x 36, us a step: in NEQ walls 147 (five passes over the
-// ghost-extended grid) -> 93 (7.5 + 37 + 49), periodic 74.  Taking x
+// ghost-extended grid) -> 78 (7.5 + 37 + 34), periodic 61.  Taking x
 // neighbours by lane shifts drops 40 % of the loads but waits for those at the
-// row ends in a branch: 98 and 88.
+// row ends in a branch: 5 and 14 us more.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -471,6 +471,7 @@ __device__ __forceinline__ void a3_face_thread(const Inst<double>& P, bool wall,
     a3_faces<A, false>(P, x, 0, phi, force, lam, gth, F);
 }
 
+// (three waves per SIMD: with four the wall path spills 270 registers, 78 -> 87 us)
 __global__ __attribute__((amdgpu_flat_work_group_size(1, 256), amdgpu_waves_per_eu(3))) void k_adj3_faces(
     const Inst<double>* __restrict__ Pp, const double* __restrict__ phi, const double* __restrict__ force,
     const double* __restrict__ lam, double gth, A3Blocks nb, A3Faces F)
@@ -657,7 +658,10 @@ __device__ __forceinline__ void a3_store(const Inst<double>& P, const A3Adj& R, 
     }
 }
 
-__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(4))) void k_adj3_cells(
+// (five waves per SIMD, three registers spilled: four, at 102 registers, take 92
+// us a step in walls and 74 periodic at 48 x 40 x 36, whose 4320 waves then need a
+// second round, and 5 % more at 96 x 80 x 64)
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(5))) void k_adj3_cells(
     const Inst<double>* __restrict__ Pp, const double* __restrict__ f, const double* __restrict__ force,
     const double* __restrict__ lam, double gt, double gth, A3Faces F, double* __restrict__ lam_out,
     double* __restrict__ grad)
