@@ -70,7 +70,7 @@ __device__ __forceinline__ Partials<LAT, T> partials(int q, T rho, const T* u, c
 
 // adjoint_tile.hip: one step of D2Q9 in FP64
 void adjoint_tile_launch(const Inst<double>* Pd, const Inst<double>& P, const void* f, const void* force, double gt,
-                         double gth, const void* lam, void* lam_out, void* grad, hipStream_t st);
+                         double gth, const void* lam, void* lam_out, void* grad, int n_cu, hipStream_t st);
 
 // adjoint_cells.hip: one step of D3Q19 in FP64; the meshes it takes, the scratch
 // it needs
@@ -1439,7 +1439,7 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
             if (rc != DUGKS_OK) return rc;
         }
         adjoint_tile_launch((const Inst<double>*)ctx->inst_dev, ctx->pd, f_n, force, tfac(ctx->pd, t_n),
-                            tfac(ctx->pd, t_n + 0.5 * (double)ctx->cfg.dt), lam_np1, lam_n, grad_force, st);
+                            tfac(ctx->pd, t_n + 0.5 * (double)ctx->cfg.dt), lam_np1, lam_n, grad_force, ctx->n_cu, st);
         return hip_check(ctx, hipGetLastError(), "adjoint launch");
     }
     // D3Q19 in FP64: three launches over the cells, with less scratch than the

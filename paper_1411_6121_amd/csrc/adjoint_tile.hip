@@ -21,11 +21,12 @@
 //   of the pair -> transposed derivative -> phi -> Eq. (f_bar_+) -> lam_n.
 //
 // Bound by FP64 issue and latency, not by memory (33 values a cell, all in
-// the cache): about 1500 instructions a lane on eight waves.  32 x 16 lanes
-// for 28 x 12 cells: one workgroup of two waves per SIMD has the 256 registers
-// that a pair of cells takes without spills, and 256^2 fills the card in one
-// round.  256^2 periodic: 21.0 us (two launches: faces, then cells) -> 12.0;
-// 200 x 150 in a box of NEQ walls, stretched: 39 us (five launches) -> 14.8.
+// the cache): about 1500 instructions a lane.  Two waves per SIMD have the 256
+// registers that a pair of cells takes without spills: one workgroup of 32 x 16
+// lanes (28 x 12 cells) per CU, or two of 32 x 8 (28 x 4 cells), which waste
+// more lanes on the halo but spread a small mesh over more CUs.  256^2 periodic:
+// 21.0 us (two launches: faces, then cells) -> 11.0; 200 x 150 in a box of NEQ
+// walls, stretched: 39 us (five launches) -> 13.2.
 #include <hip/hip_runtime.h>
 
 #include "ctx.hpp"
@@ -36,8 +37,9 @@ namespace dugks {
 
 namespace {
 
-constexpr int A2_X = 32, A2_Y = 16, A2_HALO = 2, A2_NT = A2_X * A2_Y;
-constexpr int A2_OX = A2_X - 2 * A2_HALO, A2_OY = A2_Y - 2 * A2_HALO;
+constexpr int A2_X = 32, A2_HALO = 2, A2_OX = A2_X - 2 * A2_HALO;
+// tile rows: on many cells, and on few (see adjoint_tile_us)
+constexpr int A2_ROWS = 16, A2_FEW = 8;
 
 // LDS planes of one value per lane: phi (e_y != 0, and the rest velocity), lam
 // (e_y != 0) and the force, the first eleven of them overwritten by the
@@ -271,11 +273,12 @@ __device__ __forceinline__ int a2_wrap(int i, int n)
 
 }  // namespace
 
-template <typename T>
-__global__ __attribute__((amdgpu_flat_work_group_size(A2_NT, A2_NT), amdgpu_waves_per_eu(2))) void k_adj2(
+template <typename T, int A2_Y>
+__global__ __attribute__((amdgpu_flat_work_group_size(A2_X * A2_Y, A2_X * A2_Y), amdgpu_waves_per_eu(2))) void k_adj2(
     const Inst<T>* __restrict__ Pp, const T* __restrict__ fin, const T* __restrict__ force,
     const T* __restrict__ lam_in, T gt, T gth, int tiles_x, T* __restrict__ lam_out, T* __restrict__ grad)
 {
+    constexpr int A2_NT = A2_X * A2_Y, A2_OY = A2_Y - 2 * A2_HALO;
     __shared__ T lds[A2_SLOTS * A2_NT];
     const Inst<T>& P = *Pp;
     const int blk = xcd_order((int)blockIdx.x, (int)gridDim.x);
@@ -509,13 +512,31 @@ __global__ __attribute__((amdgpu_flat_work_group_size(A2_NT, A2_NT), amdgpu_wave
     }
 }
 
-void adjoint_tile_launch(const Inst<double>* Pd, const Inst<double>& P, const void* f, const void* force, double gt,
-                         double gth, const void* lam, void* lam_out, void* grad, hipStream_t st)
+// Time of a launch in microseconds by tile rows (periodic meshes; walls add 4
+// to both): 16 rows, one workgroup per CU: 10.1 a round; 8 rows, two per CU: 7.6
+// while no CU has two, else 1.2 + 8.6 a round.  Measured, 8 against 16 rows:
+// 128^2 7.6, 10.1; 200 x 150 9.8, 10.4; 256^2 15.0, 11.0; 300^2 18.0, 19.2; 512^2
+// 42.9, 40.3.
+static double adjoint_tile_us(int rows, long long tiles, int n_cu)
 {
-    const int tiles_x = (P.n[0] + A2_OX - 1) / A2_OX, tiles_y = (P.n[1] + A2_OY - 1) / A2_OY;
-    hipLaunchKernelGGL(k_adj2<double>, dim3((unsigned)tiles_x * (unsigned)tiles_y), dim3(A2_NT), 0, st, Pd,
-                       (const double*)f, (const double*)force, (const double*)lam, gt, gth, tiles_x,
-                       (double*)lam_out, (double*)grad);
+    const long long cu = n_cu > 0 ? n_cu : 1;
+    if (rows == A2_ROWS) return 10.1 * (double)((tiles + cu - 1) / cu);
+    return tiles <= cu ? 7.6 : 1.2 + 8.6 * (double)((tiles + 2 * cu - 1) / (2 * cu));
+}
+
+void adjoint_tile_launch(const Inst<double>* Pd, const Inst<double>& P, const void* f, const void* force, double gt,
+                         double gth, const void* lam, void* lam_out, void* grad, int n_cu, hipStream_t st)
+{
+    const int tiles_x = (P.n[0] + A2_OX - 1) / A2_OX;
+    auto tiles = [&](int rows) { return (long long)tiles_x * ((P.n[1] + rows - 2 * A2_HALO - 1) / (rows - 2 * A2_HALO)); };
+    auto launch = [&](auto kern, int rows) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)tiles(rows)), dim3(A2_X * rows), 0, st, Pd, (const double*)f,
+                           (const double*)force, (const double*)lam, gt, gth, tiles_x, (double*)lam_out, (double*)grad);
+    };
+    if (adjoint_tile_us(A2_FEW, tiles(A2_FEW), n_cu) < adjoint_tile_us(A2_ROWS, tiles(A2_ROWS), n_cu))
+        launch(k_adj2<double, A2_FEW>, A2_FEW);
+    else
+        launch(k_adj2<double, A2_ROWS>, A2_ROWS);
 }
 
 }  // namespace dugks

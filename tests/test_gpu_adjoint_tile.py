@@ -1,5 +1,6 @@
-"""The one-launch D2Q9 FP64 adjoint (tiles of 28 x 12 cells, wall rules folded
-into the pairs of cells next to them) against the general reverse pass, at the
+"""The one-launch D2Q9 FP64 adjoint (tiles of 28 x 4 cells on small meshes and of
+28 x 12 on others, here the last two sizes; wall rules folded into the pairs
+of cells next to them) against the general reverse pass, at the
 edges of its tiles and of its axes.
 
 Tolerance: both evaluate the same sums of some thousand products in another
@@ -20,7 +21,7 @@ SIDES = {"box": (0,) * 6, "lid": (1, 1, 1, 1, 0, 0), "noslip": (3, 3, 3, 3, 0, 0
          "channel_x": (0, 0, 3, 1, 0, 0), "channel_y": (2, 3, 0, 0, 0, 0)}
 UW = [[0, 0.02, 0], [0, -0.01, 0], [0.03, 0, 0], [0.05, 0, 0], [0, 0, 0], [0, 0, 0]]
 SIZES = [(28, 12), (29, 13), (27, 11), (30, 14), (56, 25), (57, 24), (26, 10), (1, 1), (1, 30), (33, 1), (2, 2), (2, 40),
-         (64, 2), (3, 3), (31, 3), (150, 61)]
+         (64, 2), (3, 3), (31, 3), (150, 61), (28, 4), (29, 5), (57, 8), (250, 253), (253, 252)]
 
 
 def dev(a):
