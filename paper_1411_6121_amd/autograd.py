@@ -30,7 +30,7 @@ class _Rollout(torch.autograd.Function):
         spare = torch.empty_like(f)
         n = 0
         while n < nsteps:
-            m = min(abs(seg), nsteps - n)
+            m = min(seg, nsteps - n)
             g = torch.empty_like(f)
             dugks_step(h, f, g, force, n * dt)
             if m > 1 and dugks_run(h, g, spare, m - 1, force, (n + 1) * dt):
@@ -94,6 +94,9 @@ class _Rollout(torch.autograd.Function):
 def rollout(cfg: dict, force: torch.Tensor, u0: torch.Tensor, nsteps: int, segment: int | None = None):
     """Final velocity u(t_N) [D, nz, ny, nx] after nsteps from the equilibrium
     state at (rho0, u0) under the force field `force`; differentiable in
-    force and u0."""
-    seg = segment or max(1, math.ceil(math.sqrt(nsteps)))
-    return _Rollout.apply(force.contiguous(), u0.contiguous(), dict(cfg), int(nsteps), int(seg))
+    force and u0.  segment: steps between two checkpoints, at least 1 (None or
+    0: ceil(sqrt(nsteps)))."""
+    seg = int(segment or max(1, math.ceil(math.sqrt(nsteps))))
+    if seg < 1:
+        raise ValueError("segment must be at least 1")
+    return _Rollout.apply(force.contiguous(), u0.contiguous(), dict(cfg), int(nsteps), seg)
