@@ -333,25 +333,32 @@ __global__ __launch_bounds__(256) void k_init_one(const Inst<T>* __restrict__ Pp
     init_body<LAT, T, ORIG>(P, c, rho, u, force, gt, fout);
 }
 
-// sums over a workgroup of 256 threads of N values each, to the partials of
-// the workgroup (at most 6): in the waves by lane exchanges, between them through
-// LDS; fixed order.  The state's loads bound the kernels (128 x 100 x 90 D3Q19
-// FP64: the fields 36.0 -> 35.4 us = 6.2 TB/s, the change of two states 53.0 ->
-// 51.6 us = 6.8 TB/s against a tree in LDS with a barrier a level).
+// Sums over a workgroup of 256 threads of N values each (at most 6), to the
+// partials of the workgroup, as a binary tree over the threads (128 apart, 64,
+// .., 1): the waves first, through LDS, then the lanes of one wave by
+// exchanges.  The order is part of the result: a state's totals keep their bits.
+// Exchanges in every wave before the LDS are four times as many for the same
+// sums: fields of 4096^2 D2Q9 FP32 213 us, a tree in LDS with a barrier a level
+// 133, this 98 (D3Q19 FP64, 128 x 100 x 90, bound by its loads: 27.5 to 28).
 template <int N>
 __device__ __forceinline__ void block_sums(double (&v)[N], double* out)
 {
-    __shared__ double sh[4][N];
+    __shared__ double sh[3][N][64];
+    const int w = (int)threadIdx.x >> 6, l = (int)threadIdx.x & 63;
+    if (w > 0)
+#pragma unroll
+        for (int m = 0; m < N; ++m) sh[w - 1][m][l] = v[m];
+    __syncthreads();
+    if (w > 0) return;
+#pragma unroll
+    for (int m = 0; m < N; ++m) v[m] = (v[m] + sh[1][m][l]) + (sh[0][m][l] + sh[2][m][l]);
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1)
 #pragma unroll
         for (int m = 0; m < N; ++m) v[m] += __shfl_xor(v[m], d);
-    if ((threadIdx.x & 63) == 0)
+    if (l == 0)
 #pragma unroll
-        for (int m = 0; m < N; ++m) sh[threadIdx.x >> 6][m] = v[m];
-    __syncthreads();
-    if (threadIdx.x < N) out[threadIdx.x] = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
-    else if (threadIdx.x < 6) out[threadIdx.x] = 0.0;
+        for (int m = 0; m < 6; ++m) out[m] = m < N ? v[m < N ? m : 0] : 0.0;
 }
 
 // macroscopic fields and per-block partial totals (Eq. macro_values)
@@ -450,40 +457,36 @@ __global__ __launch_bounds__(256) void k_velocity_change(const Inst<T>* __restri
     block_sums(sum, partial + (long long)blockIdx.x * 6);
 }
 
-// Fixed-order reduction of the per-block partials (deterministic).  A thread
-// takes every 960th value, always of the same total (960 = 6 x 160), with
-// 32 loads in flight: the one workgroup waits for memory, not for
-// adds.  4500 workgroups' partials: 9.2 us (256 threads, six strided loads at
-// a time) -> 5.9 us.
-constexpr int RED_T = 960;
+// Fixed-order reduction of the per-block partials (deterministic): for each of
+// the six totals 256 chains, chain c over the blocks c, c + 256, .., then a binary
+// tree over the chains (128 apart, 64, .., 1).  A thread takes the chains c and
+// c + 128 of one total, with 48 coalesced loads in flight: the one workgroup
+// waits for memory, not for adds.  4500 blocks: 6.0 us (256 threads, six strided
+// loads at a time: 8.5).
+constexpr int RED_T = 6 * 128, RED_N = 48;
 __global__ __launch_bounds__(RED_T) void k_reduce6(const double* __restrict__ partial, int nblk, double* out)
 {
     __shared__ double sh[RED_T];
     const int t = (int)threadIdx.x;
     const long long n = (long long)nblk * 6;
-    double s = 0.0;
-    long long i = t;
-    for (; i + 31LL * RED_T < n; i += 32LL * RED_T) {
-        double v[32];
+    double s0 = 0.0, s1 = 0.0;
+    for (long long i = t; i < n; i += (long long)RED_N * RED_T) {
+        double v[RED_N];
 #pragma unroll
-        for (int k = 0; k < 32; ++k) v[k] = partial[i + (long long)k * RED_T];
+        for (int k = 0; k < RED_N; ++k) v[k] = i + (long long)k * RED_T < n ? partial[i + (long long)k * RED_T] : 0.0;
 #pragma unroll
-        for (int k = 0; k < 32; ++k) s += v[k];
+        for (int k = 0; k < RED_N; k += 2) {
+            s0 += v[k];
+            s1 += v[k + 1];
+        }
     }
-    {
-        double v[32];
-#pragma unroll
-        for (int k = 0; k < 32; ++k) v[k] = i + (long long)k * RED_T < n ? partial[i + (long long)k * RED_T] : 0.0;
-#pragma unroll
-        for (int k = 0; k < 32; ++k) s += v[k];
-    }
+    double s = s0 + s1;
     sh[t] = s;
-    __syncthreads();
-    for (int w = RED_T / 2; w >= 30; w >>= 1) {
-        if (t < w) sh[t] += sh[t + w];
+    for (int w = RED_T / 2; w >= 6; w >>= 1) {
         __syncthreads();
+        if (t < w) sh[t] = s = s + sh[t + w];
     }
-    if (t < 6) out[t] = ((sh[t] + sh[t + 6]) + (sh[t + 12] + sh[t + 18])) + sh[t + 24];
+    if (t < 6) out[t] = s;
 }
 
 static inline unsigned nblocks(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
