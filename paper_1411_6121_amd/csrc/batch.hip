@@ -133,10 +133,14 @@ static int set_tiles(dugks_batch* b, int steps)
     if (b->tiles_dev[steps]) return DUGKS_OK;
     std::vector<TileBlock> blocks;
     for (int i = 0; i < b->n; ++i) tile_blocks(i, b->cfgs[i].n[0], b->cfgs[i].n[1], steps, blocks);
-    if (hipMalloc((void**)&b->tiles_dev[steps], sizeof(TileBlock) * blocks.size()) != hipSuccess)
+    TileBlock* table = nullptr;
+    if (hipMalloc((void**)&table, sizeof(TileBlock) * blocks.size()) != hipSuccess)
         return bfail(b, DUGKS_ENOMEM, "batch table allocation");
-    if (hipMemcpy(b->tiles_dev[steps], blocks.data(), sizeof(TileBlock) * blocks.size(), hipMemcpyHostToDevice) != hipSuccess)
+    if (hipMemcpy(table, blocks.data(), sizeof(TileBlock) * blocks.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        (void)hipFree(table);
         return bfail(b, DUGKS_EHIP, "batch geometry upload");
+    }
+    b->tiles_dev[steps] = table;  // whole: later calls take it as it is
     return DUGKS_OK;
 }
 

@@ -1,0 +1,66 @@
+"""The host side where the runtime fails or a count is extreme, on a device that
+runs nothing (fake_device.c, in a process of its own): no GPU is used."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, sys
+fake = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+for n in ("fake_launches", "fake_uploads"): getattr(fake, n).argtypes = [ctypes.c_longlong]
+for n in ("fake_launch_count", "fake_upload_count"): getattr(fake, n).restype = ctypes.c_longlong
+for n in ("fake_upload_bytes", "fake_held_bytes"): getattr(fake, n).restype = ctypes.c_size_t
+import paper_1411_6121_amd as M
+lib = M.load()
+VP = ctypes.c_void_p
+def cfg(n, **kw):
+    return dict(dict(lattice=9, dtype="f64", n=n, L=tuple(float(v) for v in n), rho0=1.0, RT=1/3, tau=0.4, dt=0.2,
+                     bc=(0,) * 6), **kw)
+def batch(cfgs):
+    keep = [M.config(c) for c in cfgs]
+    b = VP()
+    rc = lib.dugks_batch_create((M.Config * len(keep))(*keep), len(keep), (ctypes.c_int64 * len(keep))(), None,
+                                ctypes.byref(b))
+    return rc, b
+def context(c):
+    h = VP()
+    assert lib.dugks_init(ctypes.byref(M.config(c)), None, None, None, VP(4096), None, ctypes.byref(h)) == M.OK
+    return h
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "fake_device.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-w", "-o", so, os.path.join(HERE, "fake_device.c")], check=True)
+    return so
+
+
+def run(fake, body):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + body, fake], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
+
+
+def test_table_that_was_not_uploaded_is_not_used(fake):
+    # the autotuner tries one step per launch more than the batch has tables
+    # for; where that table's upload fails, the next call must not take it
+    run(fake, """
+rc, b = batch([cfg((300, 200, 1))] * 20)
+assert rc == M.OK
+t, c = ctypes.c_int(), ctypes.c_int()
+args = (b, VP(4096), VP(8192), None, None, 2, None, ctypes.byref(t), ctypes.byref(c))
+for _ in range(2):
+    fake.fake_uploads(0)
+    assert lib.dugks_batch_tune(*args) == M.EHIP
+fake.fake_uploads(-1)
+held = fake.fake_held_bytes()
+assert lib.dugks_batch_tune(*args) == M.OK
+assert fake.fake_upload_count() > 0 and fake.fake_held_bytes() > held
+lib.dugks_batch_destroy(b)
+assert fake.fake_held_bytes() == 0
+""")
