@@ -32,10 +32,9 @@ void row_tile_shape(int* bx, int* by);
 // FP64 D2Q9: the tile kernel
 long long tile_count(int nx, int ny, int steps);
 int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu);
-std::vector<int> tile_plan(int nsteps, int most);
 void tile_blocks(int inst, int nx, int ny, int steps, std::vector<TileBlock>& out);
 hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
-                             const void* forces, void* fout, const long long* step0, int step, int steps,
+                             const void* forces, void* fout, const long long* step0, long long step, int steps,
                              hipStream_t st);
 
 // batch clock: set (reset != 0: s = add) or advance (s += add) the
@@ -331,7 +330,7 @@ extern "C" int dugks_batch_init(dugks_batch* b, void* f_out, void* stream)
     return b->dtype == DUGKS_F64 ? batch_init_t<D3Q19, double>(b, f_out, st) : batch_init_t<D3Q19, float>(b, f_out, st);
 }
 
-static int batch_launch_any(dugks_batch* b, const void* fin, void* fout, const void* forces, int step, int steps,
+static int batch_launch_any(dugks_batch* b, const void* fin, void* fout, const void* forces, long long step, int steps,
                             hipStream_t st)
 {
     // without any field the field-free kernels run (as for single instances)
@@ -342,38 +341,41 @@ static int batch_launch_any(dugks_batch* b, const void* fin, void* fout, const v
                               steps, st);
     } else if (b->dtype == DUGKS_F64) {
         row_batch_launch<D3Q19, double>(b->insts_dev, b->bstart_dev, b->geom_dev, b->n, b->nblocks, fin, fz, fout,
-                                        b->step_dev, step, st);
+                                        b->step_dev, (int)step, st);
         e = hipGetLastError();
     } else {
         e = f32_batch_launch(b->lattice, b->uniform, b->tile, b->insts_dev, b->bstart_dev, b->geom_dev, b->n, b->nblocks,
-                             fin, fz, fout, b->step_dev, step, st);
+                             fin, fz, fout, b->step_dev, (int)step, st);
     }
     return e == hipSuccess ? DUGKS_OK : bfail(b, DUGKS_EHIP, hipGetErrorString(e));
 }
 
-// the launches of `plan` (steps of each), then the clock
-static int launch_plan(dugks_batch* b, const void* f_in, void* f_out, const void* forces, const std::vector<int>& plan,
-                       hipStream_t st)
+// `launches` launches of steps(i) steps each, then the clock
+template <class F>
+static int launch_all(dugks_batch* b, const void* f_in, void* f_out, const void* forces, long long launches, F steps,
+                      hipStream_t st)
 {
     const void* cur = f_in;
     void* nxt = f_out;
-    int nsteps = 0;
-    for (const int s : plan) {
-        const int rc = batch_launch_any(b, cur, nxt, forces, nsteps, s, st);
+    long long done = 0;
+    for (long long i = 0; i < launches; ++i) {
+        const int s = steps(i);
+        const int rc = batch_launch_any(b, cur, nxt, forces, done, s, st);
         if (rc != DUGKS_OK) return rc;
-        nsteps += s;
+        done += s;
         void* tmp = const_cast<void*>(cur);
         cur = nxt;
         nxt = tmp;
     }
-    hipLaunchKernelGGL(k_batch_clock, dim3(1), dim3(1), 0, st, b->step_dev, (long long)nsteps, 0);
+    hipLaunchKernelGGL(k_batch_clock, dim3(1), dim3(1), 0, st, b->step_dev, done, 0);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? DUGKS_OK : bfail(b, DUGKS_EHIP, hipGetErrorString(e));
 }
 
 static int launch_run(dugks_batch* b, const void* f_in, void* f_out, const void* forces, int nsteps, hipStream_t st)
 {
-    return launch_plan(b, f_in, f_out, forces, tile_plan(nsteps, b->tiled ? b->most : 1), st);
+    const TilePlan plan(nsteps, b->tiled ? b->most : 1);
+    return launch_all(b, f_in, f_out, forces, plan.launches(), [&](long long i) { return plan.steps(i); }, st);
 }
 
 // per-instance force offsets into the instance table (before any launch)
@@ -471,10 +473,10 @@ extern "C" int dugks_batch_tune(dugks_batch* b, void* f_a, void* f_b, const void
     int best_tile = 0, best_chunk = 0, rc = DUGKS_OK;
     // time per step of nsteps launches of `steps` steps after a warm-up one
     auto timed = [&](int steps, float& ms) {
-        const std::vector<int> warm(1, steps), plan(nsteps, steps);
-        int r = launch_plan(b, f_a, f_b, forces, warm, st);
+        auto all = [&](long long) { return steps; };
+        int r = launch_all(b, f_a, f_b, forces, 1, all, st);
         if (r == DUGKS_OK && hipEventRecord(e0, st) != hipSuccess) r = bfail(b, DUGKS_EHIP, "event record");
-        if (r == DUGKS_OK) r = launch_plan(b, f_a, f_b, forces, plan, st);
+        if (r == DUGKS_OK) r = launch_all(b, f_a, f_b, forces, nsteps, all, st);
         if (r == DUGKS_OK && hipEventRecord(e1, st) != hipSuccess) r = bfail(b, DUGKS_EHIP, "event record");
         if (r == DUGKS_OK && (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
             r = bfail(b, DUGKS_EHIP, "event timing");

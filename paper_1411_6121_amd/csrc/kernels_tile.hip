@@ -400,8 +400,8 @@ __global__ TILE_BOUNDS((SMALL ? 2 : 4)) void k_tile(const Inst<T>* __restrict__ 
 template <typename T, bool FIELD>
 __global__ TILE_BOUNDS(4) void k_tile_batch(const Inst<T>* __restrict__ insts, const TileBlock* __restrict__ blocks,
                                             const T* __restrict__ fin, const T* __restrict__ forces,
-                                            T* __restrict__ fout, const long long* __restrict__ step0, int step,
-                                            int steps)
+                                            T* __restrict__ fout, const long long* __restrict__ step0,
+                                            long long step, int steps)
 {
     __shared__ T lds[TILE_SLOTS * TILE_NT];
     const TileBlock k = blocks[xcd_order((int)blockIdx.x, (int)gridDim.x)];
@@ -462,22 +462,6 @@ static int best_steps(int n_cu, F tiles_of)
     return best;
 }
 
-// Launches of a run of nsteps steps with at most `most` steps each, as steps
-// per launch.  The run ends in the buffer that steps of their own would end
-// in (as many launches as steps, modulo 2), with the state before the last
-// step in the other one: the last launch is one step.
-std::vector<int> tile_plan(int nsteps, int most)
-{
-    std::vector<int> plan;
-    if (nsteps < 1) return plan;
-    const int n = nsteps - 1;
-    int m = (n + most - 1) / most;
-    if ((m ^ n) & 1) ++m;  // m <= n: n itself has the right parity
-    for (int i = 0; i < m; ++i) plan.push_back((int)((long long)n * (i + 1) / m - (long long)n * i / m));
-    plan.push_back(1);
-    return plan;
-}
-
 template <typename T, bool UNI, bool ACC, bool FIELD, bool ORIG>
 static int launch_tile(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t0,
                        long long k0, int steps, hipStream_t st)
@@ -529,7 +513,9 @@ int tile_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0,
     void* cur = f_a;
     void* nxt = f_b;
     long long k = 0;
-    for (int s : tile_plan(nsteps, most)) {
+    const TilePlan plan(nsteps, most);
+    for (long long i = 0; i < plan.launches(); ++i) {
+        const int s = plan.steps(i);
         const int rc = tile_steps(ctx, cur, nxt, force, t0, k, s, st);
         if (rc != DUGKS_OK) return rc;
         std::swap(cur, nxt);
@@ -552,7 +538,7 @@ int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu)
 // `steps` steps of every instance; blocks: the nblocks workgroups of a launch of
 // `steps` steps
 hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
-                             const void* forces, void* fout, const long long* step0, int step, int steps,
+                             const void* forces, void* fout, const long long* step0, long long step, int steps,
                              hipStream_t st)
 {
     auto kern = forces ? k_tile_batch<double, true> : k_tile_batch<double, false>;

@@ -102,6 +102,20 @@ __host__ __device__ constexpr int max_waves_per_eu()
 // the D2Q9 tile kernel takes 1 .. TILE_MAX_STEPS time steps per launch
 constexpr int TILE_MAX_STEPS = 6;
 
+// Launches of a run of nsteps steps with at most `most` steps each.  The run ends
+// in the buffer that steps of their own would end in (as many launches as steps,
+// modulo 2), with the state before the last step in the other one: the last
+// launch is one step.
+struct TilePlan {
+    long long n, m;  // n steps in m launches, then one step (none: n = -1)
+    TilePlan(int nsteps, int most) : n((long long)nsteps - 1), m(n > 0 ? (n + most - 1) / most : 0)
+    {
+        if (n > 0 && ((m ^ n) & 1)) ++m;  // m <= n: n itself has the right parity
+    }
+    long long launches() const { return n < 0 ? 0 : m + 1; }
+    int steps(long long i) const { return i == m ? 1 : (int)(n * (i + 1) / m - n * i / m); }
+};
+
 // one workgroup of a batched launch of it: its instance and tile
 struct TileBlock {
     int inst, bx, by, pad;

@@ -64,3 +64,35 @@ assert fake.fake_upload_count() > 0 and fake.fake_held_bytes() > held
 lib.dugks_batch_destroy(b)
 assert fake.fake_held_bytes() == 0
 """)
+
+
+@pytest.mark.parametrize("lattice,dtype", [(9, "f64"), (9, "f32"), (19, "f64"), (19, "f32")])
+@pytest.mark.parametrize("batched", [False, True])
+def test_any_step_count_is_taken_launch_by_launch(fake, lattice, dtype, batched):
+    # the largest step counts: nothing is held per step (2 GiB of address space
+    # for the whole process), and the run goes on until a launch fails
+    run(fake, f"""
+c = cfg((40, 20, 1) if {lattice} == 9 else (8, 8, 8), lattice={lattice}, dtype="{dtype}")
+if {batched}: rc, h = batch([c]); assert rc == M.OK
+else: h = context(c)
+import resource
+resource.setrlimit(resource.RLIMIT_AS, (2 << 30, 2 << 30))
+w = ctypes.c_int()
+for n in (2**31 - 1, 2**31 - 2, 2**31 - 9):
+    fake.fake_launches(50)
+    if {batched}: rc = lib.dugks_batch_run(h, VP(4096), VP(8192), None, None, n, 0, None, ctypes.byref(w))
+    else: rc = lib.dugks_run(h, VP(4096), VP(8192), None, 0.0, n, None, ctypes.byref(w))
+    assert rc == M.EHIP and fake.fake_launch_count() == 50, (n, rc, fake.fake_launch_count())
+""")
+
+
+def test_tuning_steps_are_taken_launch_by_launch(fake):
+    run(fake, """
+rc, b = batch([cfg((300, 200, 1))] * 20)
+import resource
+resource.setrlimit(resource.RLIMIT_AS, (2 << 30, 2 << 30))
+t, c = ctypes.c_int(), ctypes.c_int()
+fake.fake_launches(50)
+rc = lib.dugks_batch_tune(b, VP(4096), VP(8192), None, None, 2**31 - 1, None, ctypes.byref(t), ctypes.byref(c))
+assert rc == M.EHIP and fake.fake_launch_count() == 50
+""")
