@@ -32,7 +32,7 @@ void row_tile_shape(int* bx, int* by);
 // FP64 D2Q9: the tile kernel
 long long tile_count(int nx, int ny, int steps);
 int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu);
-void tile_blocks(int inst, int nx, int ny, int steps, std::vector<TileBlock>& out);
+void tile_grid(int nx, int ny, int steps, int* tiles_x, int* tiles_y);
 hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
                              const void* forces, void* fout, const long long* step0, long long step, int steps,
                              hipStream_t st);
@@ -126,16 +126,34 @@ static int device_cus()
 }
 
 // tile kernel: the workgroups of a launch of `steps` steps per instance, uploaded
-// on first use (synchronously, never inside a capture)
+// on first use (synchronously, never inside a capture), 16 MiB at a time
 static int set_tiles(dugks_batch* b, int steps)
 {
     if (b->tiles_dev[steps]) return DUGKS_OK;
-    std::vector<TileBlock> blocks;
-    for (int i = 0; i < b->n; ++i) tile_blocks(i, b->cfgs[i].n[0], b->cfgs[i].n[1], steps, blocks);
     TileBlock* table = nullptr;
-    if (hipMalloc((void**)&table, sizeof(TileBlock) * blocks.size()) != hipSuccess)
+    if (hipMalloc((void**)&table, sizeof(TileBlock) * (size_t)b->tblocks[steps]) != hipSuccess)
         return bfail(b, DUGKS_ENOMEM, "batch table allocation");
-    if (hipMemcpy(table, blocks.data(), sizeof(TileBlock) * blocks.size(), hipMemcpyHostToDevice) != hipSuccess) {
+    const size_t piece = std::min((size_t)1 << 20, (size_t)b->tblocks[steps]);
+    std::vector<TileBlock> blocks;
+    blocks.reserve(piece);
+    TileBlock* to = table;
+    bool ok = true;
+    auto flush = [&]() {
+        ok = ok && hipMemcpy(to, blocks.data(), sizeof(TileBlock) * blocks.size(), hipMemcpyHostToDevice) == hipSuccess;
+        to += blocks.size();
+        blocks.clear();
+    };
+    for (int i = 0; i < b->n && ok; ++i) {
+        int tx, ty;
+        tile_grid(b->cfgs[i].n[0], b->cfgs[i].n[1], steps, &tx, &ty);
+        for (int by = 0; by < ty; ++by)
+            for (int bx = 0; bx < tx; ++bx) {
+                blocks.push_back(TileBlock{i, bx, by, 0});
+                if (blocks.size() == piece) flush();
+            }
+    }
+    if (ok && !blocks.empty()) flush();
+    if (!ok) {
         (void)hipFree(table);
         return bfail(b, DUGKS_EHIP, "batch geometry upload");
     }
@@ -166,10 +184,7 @@ static int choose_most(dugks_batch* b)
         b->tblocks[s] = 0;
         for (int i = 0; i < b->n; ++i) b->tblocks[s] += tile_count(nx[i], ny[i], s);
     }
-    // (a table of workgroups also has to fit the host's memory)
-    if (b->tblocks[1] > (1LL << 26)) return bfail(b, DUGKS_EUNSUPPORTED, "batch too large for one launch");
     b->model = tile_batch_steps(b->n, nx.data(), ny.data(), device_cus());
-    while (b->tblocks[b->model] > (1LL << 26)) --b->model;
     return set_most(b, b->model);
 }
 
@@ -488,7 +503,7 @@ extern "C" int dugks_batch_tune(dugks_batch* b, void* f_a, void* f_b, const void
         int best_steps = b->model;
         for (int tile = 0; tile < 3 && rc == DUGKS_OK; ++tile) {
             const int steps = b->model + (tile == 1 ? -1 : tile == 2 ? 1 : 0);
-            if (steps < 1 || steps > TILE_MAX_STEPS || b->tblocks[steps] > (1LL << 26)) continue;
+            if (steps < 1 || steps > TILE_MAX_STEPS) continue;
             float ms = 0.0f;
             rc = set_tiles(b, steps);
             if (rc == DUGKS_OK) rc = timed(steps, ms);

@@ -467,7 +467,7 @@ static int launch_tile(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* 
                        long long k0, int steps, hipStream_t st)
 {
     const long long nb = tile_count(P.n[0], P.n[1], steps);
-    if (nb > 0x7fffffffLL) return fail(ctx, DUGKS_EUNSUPPORTED, "mesh too large for one launch");
+    if (nb * TILE_NT > 0xffffffffLL) return fail(ctx, DUGKS_EUNSUPPORTED, "mesh too large for one launch");
     const int ox = TILE_X - 2 * steps, tiles_x = (P.n[0] + ox - 1) / ox;
     auto kern = (nb <= ctx->n_cu && !(P.per[0] && P.per[1])) ? k_tile<T, UNI, ACC, FIELD, ORIG, true>
                                                              : k_tile<T, UNI, ACC, FIELD, ORIG, false>;
@@ -536,23 +536,31 @@ int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu)
 }
 
 // `steps` steps of every instance; blocks: the nblocks workgroups of a launch of
-// `steps` steps
+// `steps` steps.  (In parts where they are many: a launch holds less than 2^32
+// threads.)
 hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
                              const void* forces, void* fout, const long long* step0, long long step, int steps,
                              hipStream_t st)
 {
+    constexpr long long PART = 1LL << 22;
+    static_assert(PART * TILE_NT < (1LL << 32), "threads of a launch");
     auto kern = forces ? k_tile_batch<double, true> : k_tile_batch<double, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(TILE_NT), 0, st, (const Inst<double>*)insts, blocks,
-                       (const double*)fin, (const double*)forces, (double*)fout, step0, step, steps);
-    return hipGetLastError();
+    for (long long b = 0; b < nblocks; b += PART) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)std::min(PART, nblocks - b)), dim3(TILE_NT), 0, st,
+                           (const Inst<double>*)insts, blocks + b, (const double*)fin, (const double*)forces,
+                           (double*)fout, step0, step, steps);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
-// the workgroups of a launch of `steps` steps on instance `inst` of nx x ny cells
-void tile_blocks(int inst, int nx, int ny, int steps, std::vector<TileBlock>& out)
+// tiles of a launch of `steps` steps on an nx x ny mesh along each axis
+void tile_grid(int nx, int ny, int steps, int* tiles_x, int* tiles_y)
 {
     const int ox = TILE_X - 2 * steps, oy = TILE_Y - 2 * steps;
-    for (int by = 0; by * oy < ny; ++by)
-        for (int bx = 0; bx * ox < nx; ++bx) out.push_back(TileBlock{inst, bx, by, 0});
+    *tiles_x = (nx + ox - 1) / ox;
+    *tiles_y = (ny + oy - 1) / oy;
 }
 
 }  // namespace dugks

@@ -39,14 +39,14 @@ hipError_t hipFree(void* p)
     munmap(m, *m + 4096);
     return hipSuccess;
 }
-/* kind 1: to the device; more than 64 MiB are counted only */
+/* kind 1: to the device; 1 MiB and more are counted only */
 hipError_t hipMemcpy(void* d, const void* s, size_t n, int kind)
 {
     if (kind == 1) {
         if (upload_limit >= 0 && uploads >= upload_limit) return hipErrorUnknown;
         ++uploads;
         upload_bytes += n;
-        if (n > ((size_t)64 << 20)) return hipSuccess;
+        if (n >= ((size_t)1 << 20)) return hipSuccess;
     }
     memcpy(d, s, n);
     return hipSuccess;

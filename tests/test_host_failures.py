@@ -96,3 +96,25 @@ fake.fake_launches(50)
 rc = lib.dugks_batch_tune(b, VP(4096), VP(8192), None, None, 2**31 - 1, None, ctypes.byref(t), ctypes.byref(c))
 assert rc == M.EHIP and fake.fake_launch_count() == 50
 """)
+
+
+def test_batch_of_very_many_tiles_is_created(fake):
+    # more than 2^26 tiles of 30 x 14 cells: their tables go to the device in
+    # pieces (the host holds less than half a GiB at any time)
+    run(fake, """
+rc, b = batch([cfg((40, 20, 1))])  # (the runtime's own start)
+lib.dugks_batch_destroy(b)
+fake.fake_uploads(-1)
+rc, b = batch([cfg((170000, 170000, 1))])
+assert rc == M.OK, lib.dugks_batch_last_error(None)
+peak = int([l for l in open("/proc/self/status") if l.startswith("VmHWM")][0].split()[1]) >> 10
+assert peak < 512, peak  # MiB
+tiles = -(-170000 // 30) * -(-170000 // 14)
+assert tiles > 2**26 and fake.fake_upload_bytes() >= 16 * tiles
+# and its launches (single steps: a run of one) hold less than 2^32 threads each
+fake.fake_launches(-1)
+assert lib.dugks_batch_run(b, VP(4096), VP(8192), None, None, 1, 0, None, None) == M.OK
+assert fake.fake_launch_count() > tiles * 512 // 2**32 + 1
+lib.dugks_batch_destroy(b)
+assert fake.fake_held_bytes() == 0
+""")
