@@ -30,9 +30,8 @@ void row_batch_launch(const void* insts, const long long* bstart, const BatchGeo
 int row_chunk_of(long long tiles, int nz, long long slots);
 void row_tile_shape(int* bx, int* by);
 // FP64 D2Q9: the tile kernel
-long long tile_count(int nx, int ny, int steps);
 int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu);
-void tile_grid(int nx, int ny, int steps, int* tiles_x, int* tiles_y);
+void tile_grid(int nx, int ny, int shape, int steps, int* tiles_x, int* tiles_y);
 hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
                              const void* forces, void* fout, const long long* step0, long long step, int steps,
                              hipStream_t st);
@@ -145,7 +144,7 @@ static int set_tiles(dugks_batch* b, int steps)
     };
     for (int i = 0; i < b->n && ok; ++i) {
         int tx, ty;
-        tile_grid(b->cfgs[i].n[0], b->cfgs[i].n[1], steps, &tx, &ty);
+        tile_grid(b->cfgs[i].n[0], b->cfgs[i].n[1], 0, steps, &tx, &ty);
         for (int by = 0; by < ty; ++by)
             for (int bx = 0; bx < tx; ++bx) {
                 blocks.push_back(TileBlock{i, bx, by, 0});
@@ -182,7 +181,11 @@ static int choose_most(dugks_batch* b)
     }
     for (int s = 1; s <= TILE_MAX_STEPS; ++s) {
         b->tblocks[s] = 0;
-        for (int i = 0; i < b->n; ++i) b->tblocks[s] += tile_count(nx[i], ny[i], s);
+        for (int i = 0; i < b->n; ++i) {
+            int tx, ty;
+            tile_grid(nx[i], ny[i], 0, s, &tx, &ty);
+            b->tblocks[s] += (long long)tx * ty;
+        }
     }
     b->model = tile_batch_steps(b->n, nx.data(), ny.data(), device_cus());
     return set_most(b, b->model);

@@ -9,6 +9,17 @@
 #include "../../include/dugks.h"
 #include "inst.hpp"
 
+namespace dugks {
+// The D2Q9 tile kernel: tiles of 32 x 16 cells take 1 .. TILE_MAX_STEPS time steps
+// per launch, the flat ones (32 x 8, 32 x 6, 64 x 4) one.  TilePick: how the
+// launches of a run take a mesh.
+constexpr int TILE_MAX_STEPS = 6, TILE_SHAPES = 4;
+struct TilePick {
+    int shape = 0, steps = 1;  // steps: the most of a launch
+    bool alone = false;        // every tile on the wall body, at two waves per SIMD
+};
+}  // namespace dugks
+
 struct dugks_ctx {
     dugks_config cfg;
     int D = 0, Q = 0, esize = 0;
@@ -24,6 +35,7 @@ struct dugks_ctx {
     std::string err;
     int fast = 0;                 // fused-kernel variant selected at init (0 = none)
     int chunk = 0;                // planes marched per workgroup (0 = automatic)
+    dugks::TilePick tile_one, tile_many;  // FP64 D2Q9: of a launch of one step, and of several
     int n_cu = 0;                 // compute units of the device the context was created on
     int device = -1;              // ordinal of that device
     void* adj = nullptr;          // adjoint scratch (device, lazily)

@@ -611,8 +611,8 @@ static int launch_fused2(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void
     return launch_fused2_ff<LAT, T, BX, BY, MINW, PF, false, false>(ctx, P, fin, fout, force, t, st, chunk);
 }
 
-int tile_steps(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t0, long long k0, int steps,
-               hipStream_t st);
+void tile_setup(dugks_ctx* ctx);
+int tile_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t, hipStream_t st);
 template <class LAT, typename T>
 int row_step(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t, hipStream_t st,
              int chunk);
@@ -633,6 +633,7 @@ static int default_f32_kernel(int lattice, bool uniform, bool field)
 int setup_fast(dugks_ctx* ctx)
 {
     ctx->fast = 0;
+    if (ctx->cfg.lattice == DUGKS_D2Q9 && ctx->cfg.dtype == DUGKS_F64) tile_setup(ctx);
     const char* env = getenv("DUGKS_FORCE_GENERAL");
     if (env && env[0] == '1') return DUGKS_OK;
     // 1: every face evaluated by both neighbours; 2: faces evaluated once (one
@@ -678,7 +679,7 @@ int fast_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, do
     const bool f64 = ctx->cfg.dtype == DUGKS_F64;
     if (variant == 3) {
         if (!f64) return split_step(ctx, fin, fout, force, t, st, chunk);
-        if (ctx->cfg.lattice == DUGKS_D2Q9) return tile_steps(ctx, fin, fout, force, t, 0, 1, st);
+        if (ctx->cfg.lattice == DUGKS_D2Q9) return tile_step(ctx, fin, fout, force, t, st);
         if (ctx->cfg.lattice == DUGKS_D3Q19) return row_step<D3Q19, double>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
         return row_step<D3Q27, double>(ctx, ctx->pd, fin, fout, force, t, st, chunk);
     }

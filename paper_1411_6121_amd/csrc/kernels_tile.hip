@@ -1,5 +1,6 @@
 // kernels_tile.hip -- the FP64 D2Q9 step on tiles of 32 x 16 cells, one lane per
-// cell, several time steps per launch.
+// cell, several time steps per launch; on flatter tiles, one step per launch,
+// where most of those would be halo or hold a wall.
 //
 // A workgroup loads a tile of the state into registers and advances it S
 // steps; cells within S of the tile's edge lose their neighbours one layer
@@ -22,12 +23,13 @@
 // step per launch: 1024^2 cavity FP64 28.7 against 52.7, 128^2 stretched cavity FP64 3.5 against 8.95, 40 x 20 channel FP64 3.8
 // against 8.9, 64 uneven instances FP64 126 against 175.  A march along y with
 // the rows in registers and no LDS (one lane per column, one step per launch)
-// took 41, 8.5 and 8.3 for the first three.
+// took 41, 8.5 and 8.3 for the first three.  Long meshes of few rows: see
+// tile_pick.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <utility>
-#include <vector>
 
 #include "ctx.hpp"
 #include "kernels_general.hpp"
@@ -36,9 +38,11 @@
 
 namespace dugks {
 
-constexpr int TILE_X = 32, TILE_Y = 16, TILE_NT = TILE_X * TILE_Y;
+// cells of a tile, halo included: along x 32 or 64 (a wave holds whole rows), a
+// multiple of 64 in all
+constexpr int TILES[TILE_SHAPES][2] = {{32, 16}, {32, 8}, {32, 6}, {64, 4}};
 constexpr int TILE_SLOTS = 19;
-static_assert(2 * TILE_MAX_STEPS < TILE_Y, "a tile needs rows of its own");
+static_assert(2 * TILE_MAX_STEPS < TILES[0][1], "a tile needs rows of its own");
 
 // LDS slots of a cell: f-bar-plus of the velocities with e_y != 0 in 0..5,
 // psi_y of those with e_x != 0 in 6..11, the rest velocity in 12, the upper y
@@ -65,10 +69,10 @@ __device__ __forceinline__ AxisCoef<T> axis_coef(const Inst<T>& P, int a, int j,
     return AxisCoef<T>{m.w[f], hc * m.gn[f], hc * m.cp[j], hc * m.cm[j], m.fdx[j] * P.c};
 }
 
-// cell of coordinate i on a periodic axis of n cells (-TILE_X < i < n + TILE_X)
+// cell of coordinate i on a periodic axis of n cells (-64 < i < n + 64)
 __device__ __forceinline__ int tile_wrap(int i, int n)
 {
-    if (n >= TILE_X) return i < 0 ? i + n : (i >= n ? i - n : i);
+    if (n >= 64) return i < 0 ? i + n : (i >= n ? i - n : i);
     return ((i % n) + n) % n;
 }
 
@@ -79,28 +83,28 @@ __device__ __forceinline__ int tile_wrap(int i, int n)
 // NW: no cell of the tile lies at or beyond a wall.  REREAD: the y stage reads
 // the cell's own values back from LDS instead of holding them in registers
 // over the x stage (the wall body at four waves per SIMD).
-template <typename T, bool UNI, bool ACC, bool FIELD, bool ORIG, bool NW, bool REREAD>
+template <typename T, int TX, int TY, bool UNI, bool ACC, bool FIELD, bool ORIG, bool NW, bool REREAD>
 __device__ __forceinline__ void tile_body(const Inst<T>& P, const T* __restrict__ fin, const T* __restrict__ force,
                                           T* __restrict__ fout, double t0, long long k0, int steps, int btx, int bty,
                                           T* lds)
 {
 #pragma clang fp contract(off)
     const int tid = (int)threadIdx.x;
-    const int cx = tid & (TILE_X - 1), r = tid / TILE_X;
+    const int cx = tid & (TX - 1), r = tid / TX;
     const int nx = P.n[0], ny = P.n[1];
     const long long nc = P.nc;
     const bool perx = P.per[0] != 0, pery = P.per[1] != 0;
-    const int gx = btx * (TILE_X - 2 * steps) - steps + cx, gy = bty * (TILE_Y - 2 * steps) - steps + r;
+    const int gx = btx * (TX - 2 * steps) - steps + cx, gy = bty * (TY - 2 * steps) - steps + r;
     // source cell: wrapped on a periodic axis; beyond a wall the nearest cell
     // (ghost columns are overwritten, what lies further is never used)
     const int sx = perx ? tile_wrap(gx, nx) : min(max(gx, 0), nx - 1);
     const int sy = pery ? tile_wrap(gy, ny) : min(max(gy, 0), ny - 1);
-    const bool own = cx >= steps && cx < TILE_X - steps && r >= steps && r < TILE_Y - steps && gx < nx && gy < ny;
+    const bool own = cx >= steps && cx < TX - steps && r >= steps && r < TY - steps && gx < nx && gy < ny;
     const bool glo = !NW && !perx && gx == -1, ghi = !NW && !perx && gx == nx;
     const bool bot = !NW && !pery && gy == 0, top = !NW && !pery && gy == ny - 1;
     // the tile holds a ghost column of the low / high x wall (workgroup-uniform)
-    const bool xlo = !NW && !perx && btx * (TILE_X - 2 * steps) - steps < 0;
-    const bool xhi = !NW && !perx && btx * (TILE_X - 2 * steps) - steps + TILE_X > nx;
+    const bool xlo = !NW && !perx && btx * (TX - 2 * steps) - steps < 0;
+    const bool xhi = !NW && !perx && btx * (TX - 2 * steps) - steps + TX > nx;
     const long long ci = (long long)sy * nx + sx;
     T f[9];
 #pragma unroll
@@ -172,8 +176,8 @@ __device__ __forceinline__ void tile_body(const Inst<T>& P, const T* __restrict_
             if (ghi) a = fma_(rxh, s2 - s1, s1);
         }
     };
-    auto at = [&](int slot, int row) -> T& { return lds[slot * TILE_NT + row * TILE_X + cx]; };
-    const int ru = min(r + 1, TILE_Y - 1), rd = max(r - 1, 0);
+    auto at = [&](int slot, int row) -> T& { return lds[(slot * TY + row) * TX + cx]; };
+    const int ru = min(r + 1, TY - 1), rd = max(r - 1, 0);
     const T hh = T(0.5) * P.h;
 
     for (int s = 0; s < steps; ++s) {
@@ -363,163 +367,210 @@ __device__ __forceinline__ void tile_body(const Inst<T>& P, const T* __restrict_
 }
 
 // does the tile, halo included, stay clear of every wall and its ghosts?
-template <typename T>
+template <int TX, int TY, typename T>
 __device__ __forceinline__ bool tile_no_wall(const Inst<T>& P, int steps, int btx, int bty)
 {
-    const int x0 = btx * (TILE_X - 2 * steps) - steps, y0 = bty * (TILE_Y - 2 * steps) - steps;
-    if (!P.per[0] && (x0 < 0 || x0 + TILE_X > P.n[0])) return false;
-    if (!P.per[1] && (y0 <= 0 || y0 + TILE_Y >= P.n[1])) return false;
+    const int x0 = btx * (TX - 2 * steps) - steps, y0 = bty * (TY - 2 * steps) - steps;
+    if (!P.per[0] && (x0 < 0 || x0 + TX > P.n[0])) return false;
+    if (!P.per[1] && (y0 <= 0 || y0 + TY >= P.n[1])) return false;
     return true;
 }
 
-// Waves per SIMD the kernel is compiled for.  Many tiles: four (two tiles per
-// CU; the body without wall code fits 128 registers, the wall body spills a
-// few).  At most one tile per CU (SMALL): two, since no more waves come; the
-// wall body then spills nothing (128^2 cavity FP64: 3.7 against 4.6 us a
-// step), and without the other body less code is fetched on a first pass.
-#define TILE_BOUNDS(W) __attribute__((amdgpu_flat_work_group_size(TILE_NT, TILE_NT), amdgpu_waves_per_eu(W)))
+// Waves per SIMD the kernel is compiled for.  Four (32 x 16: two tiles per CU) with
+// both bodies: the body without wall code fits 128 registers, the wall body
+// spills 26 (uniform mesh, no acceleration) to 73 (stretched, field, original
+// model).  ALONE, the wall body for every tile: two or three, without spills.
+// That pays where no more waves come (at most one 32 x 16 tile per CU: 128^2
+// cavity FP64 3.7 against 4.6 us a step, and less code is fetched on a first
+// pass) and where most tiles hold a wall: a wall tile's chain is three times that of
+// the others when it spills.
+#define TILE_BOUNDS(N, W) __attribute__((amdgpu_flat_work_group_size(N, N), amdgpu_waves_per_eu(W)))
 
-template <typename T, bool UNI, bool ACC, bool FIELD, bool ORIG, bool SMALL>
-__global__ TILE_BOUNDS((SMALL ? 2 : 4)) void k_tile(const Inst<T>* __restrict__ Pp, const T* __restrict__ fin,
-                                                    const T* __restrict__ force, T* __restrict__ fout, double t0,
-                                                    long long k0, int steps, int tiles_x)
+template <typename T, int TX, int TY, bool UNI, bool ACC, bool FIELD, bool ORIG, bool ALONE>
+__global__ TILE_BOUNDS(TX* TY, (ALONE ? 2 : 4)) void k_tile(const Inst<T>* __restrict__ Pp, const T* __restrict__ fin,
+                                                           const T* __restrict__ force, T* __restrict__ fout, double t0,
+                                                           long long k0, int steps, int tiles_x)
 {
-    __shared__ T lds[TILE_SLOTS * TILE_NT];
+    __shared__ T lds[TILE_SLOTS * TX * TY];
     const int b = xcd_order((int)blockIdx.x, (int)gridDim.x);
     const Inst<T>& P = *Pp;
     const int bx = b % tiles_x, by = b / tiles_x;
-    if (!SMALL && tile_no_wall(P, steps, bx, by))
-        tile_body<T, UNI, ACC, FIELD, ORIG, true, false>(P, fin, force, fout, t0, k0, steps, bx, by, lds);
+    if (!ALONE && tile_no_wall<TX, TY>(P, steps, bx, by))
+        tile_body<T, TX, TY, UNI, ACC, FIELD, ORIG, true, false>(P, fin, force, fout, t0, k0, steps, bx, by, lds);
     else
-        tile_body<T, UNI, ACC, FIELD, ORIG, false, false>(P, fin, force, fout, t0, k0, steps, bx, by, lds);
+        tile_body<T, TX, TY, UNI, ACC, FIELD, ORIG, false, false>(P, fin, force, fout, t0, k0, steps, bx, by, lds);
 }
 
 // many instances in one launch: blocks[b] is the instance and the tile of
 // workgroup b in XCD order; instance i is at time index *step0 + step (a device
 // counter, so a captured graph replays with advancing time)
 template <typename T, bool FIELD>
-__global__ TILE_BOUNDS(4) void k_tile_batch(const Inst<T>* __restrict__ insts, const TileBlock* __restrict__ blocks,
-                                            const T* __restrict__ fin, const T* __restrict__ forces,
-                                            T* __restrict__ fout, const long long* __restrict__ step0,
-                                            long long step, int steps)
+__global__ TILE_BOUNDS(TILES[0][0] * TILES[0][1], 4) void k_tile_batch(const Inst<T>* __restrict__ insts,
+                                                                      const TileBlock* __restrict__ blocks,
+                                                                      const T* __restrict__ fin, const T* __restrict__ forces,
+                                                                      T* __restrict__ fout, const long long* __restrict__ step0,
+                                                                      long long step, int steps)
 {
-    __shared__ T lds[TILE_SLOTS * TILE_NT];
+    constexpr int TX = TILES[0][0], TY = TILES[0][1];
+    __shared__ T lds[TILE_SLOTS * TX * TY];
     const TileBlock k = blocks[xcd_order((int)blockIdx.x, (int)gridDim.x)];
     const Inst<T>& P = insts[k.inst];
     const int bx = k.bx, by = k.by;
     const long long k0 = *step0 + step;
     const T* force = (FIELD && forces && P.foff >= 0) ? forces + P.foff : nullptr;
-    const bool nw = tile_no_wall(P, steps, bx, by);
+    const bool nw = tile_no_wall<TX, TY>(P, steps, bx, by);
     fin += P.off;
     fout += P.off;
     if (P.uni) {
-        if (nw) tile_body<T, true, true, FIELD, false, true, false>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
-        else tile_body<T, true, true, FIELD, false, false, true>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+        if (nw) tile_body<T, TX, TY, true, true, FIELD, false, true, false>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+        else tile_body<T, TX, TY, true, true, FIELD, false, false, true>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
     } else {
-        if (nw) tile_body<T, false, true, FIELD, false, true, false>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
-        else tile_body<T, false, true, FIELD, false, false, true>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+        if (nw) tile_body<T, TX, TY, false, true, FIELD, false, true, false>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
+        else tile_body<T, TX, TY, false, true, FIELD, false, false, true>(P, fin, force, fout, 0.0, k0, steps, bx, by, lds);
     }
 }
 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// tiles of a launch of `steps` steps on an nx x ny mesh
-long long tile_count(int nx, int ny, int steps)
+// tiles of a launch of `steps` steps on an nx x ny mesh along each axis
+void tile_grid(int nx, int ny, int shape, int steps, int* tiles_x, int* tiles_y)
 {
-    const int ox = TILE_X - 2 * steps, oy = TILE_Y - 2 * steps;
-    return (long long)((nx + ox - 1) / ox) * ((ny + oy - 1) / oy);
+    const int ox = TILES[shape][0] - 2 * steps, oy = TILES[shape][1] - 2 * steps;
+    *tiles_x = (nx + ox - 1) / ox;
+    *tiles_y = (ny + oy - 1) / oy;
 }
 
-// Time of a launch of `steps` steps on `tiles` tiles, in microseconds.  A
-// launch costs 4.5, a tile with its CU to itself 2.9 per step (latency), and a CU
-// with several tiles 1.5 + 1.25 per step for each.  Fitted on MI355X to 40x20 to
-// 1024^2 meshes and 1 to 6 steps a launch (1024^2: 32.6, 27.1 and 29.8 us a step
-// for 1, 2 and 3 steps a launch; 128^2 cavity: 7.4, 4.8, 4.1, 3.8, 3.7 and 3.7
-// us for 1 to 6).
-static double tile_launch_us(long long tiles, int steps, int n_cu)
+// Time of a launch of `steps` steps on `tiles` tiles in microseconds, `walls` the
+// share of them that holds a wall on the CUs that have the most of those.  A launch costs
+// 4.5, a tile with its CU to itself 2.9 per step (latency; a spilling wall body
+// 6.5), and a CU with several tiles what follows for each.  Fitted on MI355X
+// to meshes of 40 x 20 to 2048^2, 10^6 x 1 to 65536 x 64 and 16 x 65536 cells and
+// 1 to 6 steps a launch (1024^2: 32.6, 27.1 and 29.8 us a step for 1, 2 and 3
+// steps; 128^2 cavity: 7.4, 4.8, 4.1, 3.8, 3.7 and 3.7 us for 1 to 6).
+static double tile_us(int shape, int steps, bool alone, double tiles, double walls, int n_cu)
 {
-    const int cu = n_cu > 0 ? n_cu : 1;
-    const double per_cu = (double)((tiles + cu - 1) / cu);
-    return 4.5 + std::max(2.9 * steps, per_cu * (1.5 + 1.25 * steps));
+    const double cu = n_cu > 0 ? n_cu : 1, per_cu = std::ceil(tiles / cu), s = steps;
+    // per tile of a CU that has several: without a wall, with one, all on the wall body
+    static const double each[TILE_SHAPES][3] = {{0, 0, 0}, {0, 0, 1.40}, {0, 0, 1.15}, {1.15, 3.0, 1.5}};
+    if (alone) return 4.5 + std::max(2.9 * s, shape == 0 ? 0.0 : per_cu * each[shape][2]);
+    const double free_ = shape == 0 ? 1.5 + 1.25 * s : each[shape][0], wall = shape == 0 ? 3.5 + 2.9 * s : each[shape][1];
+    return 4.5 + std::max((walls > 0 ? 6.5 : 2.9) * s, per_cu * (free_ + walls * (wall - free_)));
 }
 
-// Steps per launch that give the shortest time per step: more steps save
-// launches and passes over memory, but overlap the tiles more.  `tiles_of`:
-// tiles for a number of steps per launch.
-template <class F>
-static int best_steps(int n_cu, F tiles_of)
+// How to take a mesh: the shape and steps per launch (at most `most`) of the
+// shortest time per step.  More steps save launches and passes over memory, but
+// overlap the tiles more.  Flat tiles waste fewer lanes on few rows, and alone
+// (the wall body without spills) they are the better ones while the rows of tiles at
+// the y walls are a large share: an XCD takes a range of rows, so with up to
+// eight rows of tiles one has walls only.  us a step, 32 x 16 tiles and their
+// best steps against the choice (marched rows of 128 columns before both): 10^6 x
+// 1 periodic 260 -> 72 (79), 10^6 x 2 cavity 642 -> 100 (121), 65536 x 16 cavity
+// 82 -> 40 (55), 65536 x 64 254 -> 164 (177), 16384 x 128 109 -> 92 (101).  Between
+// near equals (3 % in steps, 7 % in shape, the fit's errors) the fewer steps and
+// the taller tiles stay.  The results do not depend on the choice.
+// (32 x 16 alone: up to one tile per CU, where no more waves come; 32 x 8 and 32 x 6
+// have no other form: without walls the 64 x 4 and 32 x 16 tiles are better.)
+static TilePick tile_pick(int nx, int ny, bool wall_x, bool wall_y, int most, int n_cu)
 {
-    int best = 1;
+    TilePick best;
     double best_us = 1e300;
-    for (int s = 1; s <= TILE_MAX_STEPS; ++s) {
-        const double us = tile_launch_us(tiles_of(s), s, n_cu) / s;
-        if (us < best_us) {
-            best_us = us;
-            best = s;
+    for (int shape = 0; shape < TILE_SHAPES; ++shape)
+        for (int s = 1; s <= (shape == 0 ? most : 1); ++s) {
+            int tx, ty;
+            tile_grid(nx, ny, shape, s, &tx, &ty);
+            const double fx = wall_x ? std::max(0.0, 1.0 - 2.0 / tx) : 1.0, fy = wall_y ? std::max(0.0, 1.0 - 8.0 / ty) : 1.0;
+            const double tiles = (double)tx * ty, walls = 1.0 - fx * fy;
+            for (const bool alone : {false, true}) {
+                if (shape == 0 && alone && (tiles > n_cu || !(wall_x || wall_y))) continue;
+                if ((shape == 1 || shape == 2) && !alone) continue;
+                const double us = tile_us(shape, s, alone, tiles, walls, n_cu) / s;
+                if (us < (shape == 0 ? 0.97 : best.shape == 0 ? 0.93 : 1.0) * best_us) {
+                    best_us = us;
+                    best.shape = shape, best.steps = s, best.alone = alone;
+                }
+            }
         }
-    }
     return best;
 }
 
-template <typename T, bool UNI, bool ACC, bool FIELD, bool ORIG>
+template <typename T, bool UNI, bool ACC, bool FIELD, bool ORIG, int SHAPE, bool ALONE>
 static int launch_tile(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t0,
                        long long k0, int steps, hipStream_t st)
 {
-    const long long nb = tile_count(P.n[0], P.n[1], steps);
-    if (nb * TILE_NT > 0xffffffffLL) return fail(ctx, DUGKS_EUNSUPPORTED, "mesh too large for one launch");
-    const int ox = TILE_X - 2 * steps, tiles_x = (P.n[0] + ox - 1) / ox;
-    auto kern = (nb <= ctx->n_cu && !(P.per[0] && P.per[1])) ? k_tile<T, UNI, ACC, FIELD, ORIG, true>
-                                                             : k_tile<T, UNI, ACC, FIELD, ORIG, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(TILE_NT), 0, st, (const Inst<T>*)ctx->inst_dev, (const T*)fin,
-                       (const T*)force, (T*)fout, t0, k0, steps, tiles_x);
+    constexpr int TX = TILES[SHAPE][0], TY = TILES[SHAPE][1];
+    int tx, ty;
+    tile_grid(P.n[0], P.n[1], SHAPE, steps, &tx, &ty);
+    if ((long long)tx * ty * (TX * TY) > 0xffffffffLL) return fail(ctx, DUGKS_EUNSUPPORTED, "mesh too large for one launch");
+    hipLaunchKernelGGL((k_tile<T, TX, TY, UNI, ACC, FIELD, ORIG, ALONE>), dim3((unsigned)(tx * ty)), dim3(TX * TY), 0, st,
+                       (const Inst<T>*)ctx->inst_dev, (const T*)fin, (const T*)force, (T*)fout, t0, k0, steps, tx);
     return hip_check(ctx, hipGetLastError(), "step launch");
+}
+
+template <typename T, bool UNI, bool ACC, bool FIELD, bool ORIG>
+static int launch_tile_as(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t0,
+                          long long k0, TilePick pick, hipStream_t st)
+{
+#define DUGKS_TILE(SHAPE, ALONE) \
+    launch_tile<T, UNI, ACC, FIELD, ORIG, SHAPE, ALONE>(ctx, P, fin, fout, force, t0, k0, pick.steps, st)
+    if (pick.shape == 1) return DUGKS_TILE(1, true);
+    if (pick.shape == 2) return DUGKS_TILE(2, true);
+    if (pick.shape == 3) return pick.alone ? DUGKS_TILE(3, true) : DUGKS_TILE(3, false);
+    return pick.alone ? DUGKS_TILE(0, true) : DUGKS_TILE(0, false);
+#undef DUGKS_TILE
 }
 
 template <typename T, bool UNI, bool ORIG>
 static int launch_tile_acc(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t0,
-                           long long k0, int steps, hipStream_t st)
+                           long long k0, TilePick pick, hipStream_t st)
 {
-    if (force) return launch_tile<T, UNI, true, true, ORIG>(ctx, P, fin, fout, force, t0, k0, steps, st);
+    if (force) return launch_tile_as<T, UNI, true, true, ORIG>(ctx, P, fin, fout, force, t0, k0, pick, st);
     if (P.G0[0] != T(0) || P.G0[1] != T(0))
-        return launch_tile<T, UNI, true, false, ORIG>(ctx, P, fin, fout, force, t0, k0, steps, st);
-    return launch_tile<T, UNI, false, false, ORIG>(ctx, P, fin, fout, force, t0, k0, steps, st);
+        return launch_tile_as<T, UNI, true, false, ORIG>(ctx, P, fin, fout, force, t0, k0, pick, st);
+    return launch_tile_as<T, UNI, false, false, ORIG>(ctx, P, fin, fout, force, t0, k0, pick, st);
 }
 
-template <typename T>
-static int launch_tile_t(dugks_ctx* ctx, const Inst<T>& P, const void* fin, void* fout, const void* force, double t0,
-                         long long k0, int steps, hipStream_t st)
+// pick.steps steps from time index k0 (time t0 + k0 dt), fin -> fout
+static int tile_launch(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t0, long long k0, TilePick pick,
+                       hipStream_t st)
 {
+    const Inst<double>& P = ctx->pd;
     if (P.orig)
-        return P.uni ? launch_tile_acc<T, true, true>(ctx, P, fin, fout, force, t0, k0, steps, st)
-                     : launch_tile_acc<T, false, true>(ctx, P, fin, fout, force, t0, k0, steps, st);
-    return P.uni ? launch_tile_acc<T, true, false>(ctx, P, fin, fout, force, t0, k0, steps, st)
-                 : launch_tile_acc<T, false, false>(ctx, P, fin, fout, force, t0, k0, steps, st);
+        return P.uni ? launch_tile_acc<double, true, true>(ctx, P, fin, fout, force, t0, k0, pick, st)
+                     : launch_tile_acc<double, false, true>(ctx, P, fin, fout, force, t0, k0, pick, st);
+    return P.uni ? launch_tile_acc<double, true, false>(ctx, P, fin, fout, force, t0, k0, pick, st)
+                 : launch_tile_acc<double, false, false>(ctx, P, fin, fout, force, t0, k0, pick, st);
 }
 
-// `steps` steps from time index k0 (time t0 + k0 dt), fin -> fout
-int tile_steps(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t0, long long k0, int steps,
-               hipStream_t st)
+// the context's picks (the calls only read them)
+void tile_setup(dugks_ctx* ctx)
 {
-    return launch_tile_t<double>(ctx, ctx->pd, fin, fout, force, t0, k0, steps, st);
+    const Inst<double>& P = ctx->pd;
+    ctx->tile_one = tile_pick(P.n[0], P.n[1], !P.per[0], !P.per[1], 1, ctx->n_cu);
+    ctx->tile_many = tile_pick(P.n[0], P.n[1], !P.per[0], !P.per[1], TILE_MAX_STEPS, ctx->n_cu);
+}
+
+// one step at time t
+int tile_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, double t, hipStream_t st)
+{
+    return tile_launch(ctx, fin, fout, force, t, 0, ctx->tile_one, st);
 }
 
 // nsteps steps from f_a, as dugks_run; *which_out as there
 int tile_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0, int nsteps, hipStream_t st,
              int* which_out)
 {
-    const int nx = ctx->cfg.n[0], ny = ctx->cfg.n[1];
-    const int most = best_steps(ctx->n_cu, [&](int s) { return tile_count(nx, ny, s); });
     void* cur = f_a;
     void* nxt = f_b;
     long long k = 0;
-    const TilePlan plan(nsteps, most);
+    const TilePlan plan(nsteps, ctx->tile_many.steps);
     for (long long i = 0; i < plan.launches(); ++i) {
-        const int s = plan.steps(i);
-        const int rc = tile_steps(ctx, cur, nxt, force, t0, k, s, st);
+        TilePick pick = plan.steps(i) == 1 ? ctx->tile_one : ctx->tile_many;
+        pick.steps = plan.steps(i);
+        const int rc = tile_launch(ctx, cur, nxt, force, t0, k, pick, st);
         if (rc != DUGKS_OK) return rc;
         std::swap(cur, nxt);
-        k += s;
+        k += pick.steps;
     }
     if (which_out) *which_out = nsteps & 1;
     return DUGKS_OK;
@@ -528,11 +579,22 @@ int tile_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0,
 // steps per launch of a batch of n instances of nx[i] x ny[i] cells
 int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu)
 {
-    return best_steps(n_cu, [&](int s) {
+    int best = 1;
+    double best_us = 1e300;
+    for (int s = 1; s <= TILE_MAX_STEPS; ++s) {
         long long t = 0;
-        for (int i = 0; i < n; ++i) t += tile_count(nx[i], ny[i], s);
-        return t;
-    });
+        for (int i = 0; i < n; ++i) {
+            int tx, ty;
+            tile_grid(nx[i], ny[i], 0, s, &tx, &ty);
+            t += (long long)tx * ty;
+        }
+        const double us = tile_us(0, s, false, (double)t, 0.0, n_cu) / s;
+        if (us < best_us) {
+            best_us = us;
+            best = s;
+        }
+    }
+    return best;
 }
 
 // `steps` steps of every instance; blocks: the nblocks workgroups of a launch of
@@ -542,25 +604,18 @@ hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long lo
                              const void* forces, void* fout, const long long* step0, long long step, int steps,
                              hipStream_t st)
 {
+    constexpr int NT = TILES[0][0] * TILES[0][1];
     constexpr long long PART = 1LL << 22;
-    static_assert(PART * TILE_NT < (1LL << 32), "threads of a launch");
+    static_assert(PART * NT < (1LL << 32), "threads of a launch");
     auto kern = forces ? k_tile_batch<double, true> : k_tile_batch<double, false>;
     for (long long b = 0; b < nblocks; b += PART) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)std::min(PART, nblocks - b)), dim3(TILE_NT), 0, st,
+        hipLaunchKernelGGL(kern, dim3((unsigned)std::min(PART, nblocks - b)), dim3(NT), 0, st,
                            (const Inst<double>*)insts, blocks + b, (const double*)fin, (const double*)forces,
                            (double*)fout, step0, step, steps);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-// tiles of a launch of `steps` steps on an nx x ny mesh along each axis
-void tile_grid(int nx, int ny, int steps, int* tiles_x, int* tiles_y)
-{
-    const int ox = TILE_X - 2 * steps, oy = TILE_Y - 2 * steps;
-    *tiles_x = (nx + ox - 1) / ox;
-    *tiles_y = (ny + oy - 1) / oy;
 }
 
 }  // namespace dugks

@@ -99,9 +99,6 @@ __host__ __device__ constexpr int max_waves_per_eu()
 #define DUGKS_KERNEL_BOUNDS(NT, MINW, MAXW) \
     __attribute__((amdgpu_flat_work_group_size(1, NT), amdgpu_waves_per_eu(MINW, MAXW)))
 
-// the D2Q9 tile kernel takes 1 .. TILE_MAX_STEPS time steps per launch
-constexpr int TILE_MAX_STEPS = 6;
-
 // Launches of a run of nsteps steps with at most `most` steps each.  The run ends
 // in the buffer that steps of their own would end in (as many launches as steps,
 // modulo 2), with the state before the last step in the other one: the last
