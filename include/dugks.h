@@ -365,8 +365,9 @@ int dugks_batch_step(dugks_batch* b, void* f_in, void* f_out, const void* forces
 /*
  * Autotuner of the batched launch: times nsteps steps (after one warm-up
  * step) and keeps the fastest for later dugks_batch_run calls.  FP64 D2Q9:
- * the time steps of one launch, as the model of the batch's default has them
- * (tile variant 0), one fewer (1) or one more (2).  Else: every tile shape
+ * the tiles and time steps of one launch as the model of the batch's default
+ * has them (tile variant 0), 32 x 16 tiles with one step fewer (1) and with one
+ * more (2).  Else: every tile shape
  * (D3Q19 one; FP32 D2Q9 rows of 128, 64 or 256 columns) and every chunk policy:
  * each instance's own march chunk from the chunk model (the device's resident
  * workgroups shared among the instances in proportion to their cells; chunk 0,

@@ -30,9 +30,9 @@ void row_batch_launch(const void* insts, const long long* bstart, const BatchGeo
 int row_chunk_of(long long tiles, int nz, long long slots);
 void row_tile_shape(int* bx, int* by);
 // FP64 D2Q9: the tile kernel
-int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu);
+TilePick tile_batch_pick(int n, const int* nx, const int* ny, const unsigned char* walls, int n_cu);
 void tile_grid(int nx, int ny, int shape, int steps, int* tiles_x, int* tiles_y);
-hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
+hipError_t tile_batch_launch(int shape, const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
                              const void* forces, void* fout, const long long* step0, long long step, int steps,
                              hipStream_t st);
 
@@ -69,9 +69,11 @@ struct dugks_batch {
     int tile = 0, chunk = 0;  // tile-shape variant and march chunk (0 = default) in use
     bool uniform = true;      // every instance on a uniform mesh
     bool tiled = false;       // FP64 D2Q9: the tile kernel
-    int most = 1, model = 1;  // of it: time steps of one launch, and the model's choice
-    TileBlock* tiles_dev[TILE_MAX_STEPS + 1] = {};  // the workgroups of a launch of s steps
-    long long tblocks[TILE_MAX_STEPS + 1] = {};     // and how many they are
+    TilePick pick, model;     // of it: shape and most steps of a launch, and the model's choice
+    // the workgroups of a launch of s steps on 32 x 16 tiles (index s) or of one on
+    // tiles of shape k (TILE_MAX_STEPS + k), and how many they are
+    TileBlock* tiles_dev[TILE_MAX_STEPS + TILE_SHAPES] = {};
+    long long tblocks[TILE_MAX_STEPS + TILE_SHAPES] = {};
     bool any_field = false;   // some instance has a force field
     std::vector<dugks_config> cfgs;
     std::vector<std::vector<double>> faces_own;  // copies of custom face coordinates (cfgs[i].faces point here)
@@ -124,15 +126,25 @@ static int device_cus()
     return ncu;
 }
 
-// tile kernel: the workgroups of a launch of `steps` steps per instance, uploaded
-// on first use (synchronously, never inside a capture), 16 MiB at a time
-static int set_tiles(dugks_batch* b, int steps)
+static int tile_table(int shape, int steps) { return shape == 0 ? steps : TILE_MAX_STEPS + shape; }
+
+// tile kernel: the workgroups of a launch of `steps` steps on tiles of shape
+// `shape`, uploaded on first use (synchronously, never inside a capture), 16 MiB at
+// a time
+static int set_tiles(dugks_batch* b, int shape, int steps)
 {
-    if (b->tiles_dev[steps]) return DUGKS_OK;
+    const int id = tile_table(shape, steps);
+    if (b->tiles_dev[id]) return DUGKS_OK;
+    b->tblocks[id] = 0;
+    for (int i = 0; i < b->n; ++i) {
+        int tx, ty;
+        tile_grid(b->cfgs[i].n[0], b->cfgs[i].n[1], shape, steps, &tx, &ty);
+        b->tblocks[id] += (long long)tx * ty;
+    }
     TileBlock* table = nullptr;
-    if (hipMalloc((void**)&table, sizeof(TileBlock) * (size_t)b->tblocks[steps]) != hipSuccess)
+    if (hipMalloc((void**)&table, sizeof(TileBlock) * (size_t)b->tblocks[id]) != hipSuccess)
         return bfail(b, DUGKS_ENOMEM, "batch table allocation");
-    const size_t piece = std::min((size_t)1 << 20, (size_t)b->tblocks[steps]);
+    const size_t piece = std::min((size_t)1 << 20, (size_t)b->tblocks[id]);
     std::vector<TileBlock> blocks;
     blocks.reserve(piece);
     TileBlock* to = table;
@@ -144,7 +156,7 @@ static int set_tiles(dugks_batch* b, int steps)
     };
     for (int i = 0; i < b->n && ok; ++i) {
         int tx, ty;
-        tile_grid(b->cfgs[i].n[0], b->cfgs[i].n[1], 0, steps, &tx, &ty);
+        tile_grid(b->cfgs[i].n[0], b->cfgs[i].n[1], shape, steps, &tx, &ty);
         for (int by = 0; by < ty; ++by)
             for (int bx = 0; bx < tx; ++bx) {
                 blocks.push_back(TileBlock{i, bx, by, 0});
@@ -156,39 +168,33 @@ static int set_tiles(dugks_batch* b, int steps)
         (void)hipFree(table);
         return bfail(b, DUGKS_EHIP, "batch geometry upload");
     }
-    b->tiles_dev[steps] = table;  // whole: later calls take it as it is
+    b->tiles_dev[id] = table;  // whole: later calls take it as it is
     return DUGKS_OK;
 }
 
-// the tile kernel's launches take up to `most` steps each
-static int set_most(dugks_batch* b, int most)
+// the tile kernel's launches go as `pick` says
+static int set_pick(dugks_batch* b, TilePick pick)
 {
-    for (int s = 1; s <= most; ++s) {
-        const int rc = set_tiles(b, s);
+    for (int s = 1; s <= pick.steps; ++s) {
+        const int rc = set_tiles(b, pick.shape, s);
         if (rc != DUGKS_OK) return rc;
     }
-    b->most = most;
+    b->pick = pick;
     return DUGKS_OK;
 }
 
-// workgroups of a launch of `steps` steps, and the model's choice of `most`
-static int choose_most(dugks_batch* b)
+// the model's choice
+static int choose_pick(dugks_batch* b)
 {
     std::vector<int> nx(b->n), ny(b->n);
+    std::vector<unsigned char> walls(b->n);
     for (int i = 0; i < b->n; ++i) {
         nx[i] = b->cfgs[i].n[0];
         ny[i] = b->cfgs[i].n[1];
+        walls[i] = (b->cfgs[i].bc[0] != DUGKS_PERIODIC ? 1 : 0) | (b->cfgs[i].bc[2] != DUGKS_PERIODIC ? 2 : 0);
     }
-    for (int s = 1; s <= TILE_MAX_STEPS; ++s) {
-        b->tblocks[s] = 0;
-        for (int i = 0; i < b->n; ++i) {
-            int tx, ty;
-            tile_grid(nx[i], ny[i], 0, s, &tx, &ty);
-            b->tblocks[s] += (long long)tx * ty;
-        }
-    }
-    b->model = tile_batch_steps(b->n, nx.data(), ny.data(), device_cus());
-    return set_most(b, b->model);
+    b->model = tile_batch_pick(b->n, nx.data(), ny.data(), walls.data(), device_cus());
+    return set_pick(b, b->model);
 }
 
 // Workgroup geometry of every instance for tile-shape variant `tile` and
@@ -276,7 +282,7 @@ static int build_tables(dugks_batch* b, const int64_t* offsets, hipStream_t st)
         hipMemcpy(b->cstart_dev, cstart.data(), sizeof(long long) * (n + 1), hipMemcpyHostToDevice) != hipSuccess)
         return bfail(b, DUGKS_EHIP, "batch table upload");
     (void)st;
-    return b->tiled ? choose_most(b) : set_geometry(b, 0, 0);
+    return b->tiled ? choose_pick(b) : set_geometry(b, 0, 0);
 }
 
 extern "C" int dugks_batch_create(const dugks_config* cfgs, int n, const int64_t* offsets, void* stream,
@@ -348,15 +354,16 @@ extern "C" int dugks_batch_init(dugks_batch* b, void* f_out, void* stream)
     return b->dtype == DUGKS_F64 ? batch_init_t<D3Q19, double>(b, f_out, st) : batch_init_t<D3Q19, float>(b, f_out, st);
 }
 
-static int batch_launch_any(dugks_batch* b, const void* fin, void* fout, const void* forces, long long step, int steps,
-                            hipStream_t st)
+static int batch_launch_any(dugks_batch* b, int shape, const void* fin, void* fout, const void* forces, long long step,
+                            int steps, hipStream_t st)
 {
     // without any field the field-free kernels run (as for single instances)
     const void* fz = b->any_field ? forces : nullptr;
     hipError_t e = hipSuccess;
     if (b->tiled) {
-        e = tile_batch_launch(b->insts_dev, b->tiles_dev[steps], b->tblocks[steps], fin, fz, fout, b->step_dev, step,
-                              steps, st);
+        const int id = tile_table(shape, steps);
+        e = tile_batch_launch(shape, b->insts_dev, b->tiles_dev[id], b->tblocks[id], fin, fz, fout, b->step_dev, step, steps,
+                              st);
     } else if (b->dtype == DUGKS_F64) {
         row_batch_launch<D3Q19, double>(b->insts_dev, b->bstart_dev, b->geom_dev, b->n, b->nblocks, fin, fz, fout,
                                         b->step_dev, (int)step, st);
@@ -368,9 +375,9 @@ static int batch_launch_any(dugks_batch* b, const void* fin, void* fout, const v
     return e == hipSuccess ? DUGKS_OK : bfail(b, DUGKS_EHIP, hipGetErrorString(e));
 }
 
-// `launches` launches of steps(i) steps each, then the clock
+// `launches` launches of steps(i) steps each on tiles of shape `shape`, then the clock
 template <class F>
-static int launch_all(dugks_batch* b, const void* f_in, void* f_out, const void* forces, long long launches, F steps,
+static int launch_all(dugks_batch* b, int shape, const void* f_in, void* f_out, const void* forces, long long launches, F steps,
                       hipStream_t st)
 {
     const void* cur = f_in;
@@ -378,7 +385,7 @@ static int launch_all(dugks_batch* b, const void* f_in, void* f_out, const void*
     long long done = 0;
     for (long long i = 0; i < launches; ++i) {
         const int s = steps(i);
-        const int rc = batch_launch_any(b, cur, nxt, forces, done, s, st);
+        const int rc = batch_launch_any(b, shape, cur, nxt, forces, done, s, st);
         if (rc != DUGKS_OK) return rc;
         done += s;
         void* tmp = const_cast<void*>(cur);
@@ -392,8 +399,8 @@ static int launch_all(dugks_batch* b, const void* f_in, void* f_out, const void*
 
 static int launch_run(dugks_batch* b, const void* f_in, void* f_out, const void* forces, int nsteps, hipStream_t st)
 {
-    const TilePlan plan(nsteps, b->tiled ? b->most : 1);
-    return launch_all(b, f_in, f_out, forces, plan.launches(), [&](long long i) { return plan.steps(i); }, st);
+    const TilePlan plan(nsteps, b->pick.steps);
+    return launch_all(b, b->pick.shape, f_in, f_out, forces, plan.launches(), [&](long long i) { return plan.steps(i); }, st);
 }
 
 // per-instance force offsets into the instance table (before any launch)
@@ -490,11 +497,11 @@ extern "C" int dugks_batch_tune(dugks_batch* b, void* f_a, void* f_b, const void
     float best = -1.0f;
     int best_tile = 0, best_chunk = 0, rc = DUGKS_OK;
     // time per step of nsteps launches of `steps` steps after a warm-up one
-    auto timed = [&](int steps, float& ms) {
+    auto timed = [&](int shape, int steps, float& ms) {
         auto all = [&](long long) { return steps; };
-        int r = launch_all(b, f_a, f_b, forces, 1, all, st);
+        int r = launch_all(b, shape, f_a, f_b, forces, 1, all, st);
         if (r == DUGKS_OK && hipEventRecord(e0, st) != hipSuccess) r = bfail(b, DUGKS_EHIP, "event record");
-        if (r == DUGKS_OK) r = launch_all(b, f_a, f_b, forces, nsteps, all, st);
+        if (r == DUGKS_OK) r = launch_all(b, shape, f_a, f_b, forces, nsteps, all, st);
         if (r == DUGKS_OK && hipEventRecord(e1, st) != hipSuccess) r = bfail(b, DUGKS_EHIP, "event record");
         if (r == DUGKS_OK && (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
             r = bfail(b, DUGKS_EHIP, "event timing");
@@ -502,17 +509,22 @@ extern "C" int dugks_batch_tune(dugks_batch* b, void* f_a, void* f_b, const void
         return r;
     };
     if (b->tiled) {
-        // 0: the model's steps per launch; 1: one fewer; 2: one more
-        int best_steps = b->model;
+        // 0: the model's choice; 32 x 16 tiles with one step per launch fewer (1) and
+        // one more (2) than that (flat tiles: with one and with two)
+        TilePick best_pick = b->model;
         for (int tile = 0; tile < 3 && rc == DUGKS_OK; ++tile) {
-            const int steps = b->model + (tile == 1 ? -1 : tile == 2 ? 1 : 0);
-            if (steps < 1 || steps > TILE_MAX_STEPS) continue;
+            TilePick p = b->model;
+            if (tile > 0) {
+                p.shape = 0;
+                p.steps += b->model.shape == 0 ? 2 * tile - 3 : tile - 1;
+            }
+            if (p.steps < 1 || p.steps > TILE_MAX_STEPS) continue;
             float ms = 0.0f;
-            rc = set_tiles(b, steps);
-            if (rc == DUGKS_OK) rc = timed(steps, ms);
-            if (rc == DUGKS_OK && (best < 0.0f || ms < best)) { best = ms; best_tile = tile; best_steps = steps; }
+            rc = set_tiles(b, p.shape, p.steps);
+            if (rc == DUGKS_OK) rc = timed(p.shape, p.steps, ms);
+            if (rc == DUGKS_OK && (best < 0.0f || ms < best)) { best = ms; best_tile = tile; best_pick = p; }
         }
-        if (rc == DUGKS_OK) rc = set_most(b, best_steps);
+        if (rc == DUGKS_OK) rc = set_pick(b, best_pick);
         drop_graph(b);
     } else {
         // 0: a chunk per instance from the chunk model; else one chunk for all
@@ -523,7 +535,7 @@ extern "C" int dugks_batch_tune(dugks_batch* b, void* f_a, void* f_b, const void
                 if (chunk > 2 * maxm) continue;
                 float ms = 0.0f;
                 rc = set_geometry(b, tile, chunk);
-                if (rc == DUGKS_OK) rc = timed(1, ms);
+                if (rc == DUGKS_OK) rc = timed(0, 1, ms);
                 if (rc != DUGKS_OK) break;
                 if (best < 0.0f || ms < best) { best = ms; best_tile = tile; best_chunk = chunk; }
             }

@@ -430,6 +430,23 @@ __global__ TILE_BOUNDS(TILES[0][0] * TILES[0][1], 4) void k_tile_batch(const Ins
     }
 }
 
+// the same on flat tiles, every tile on the wall body (two waves per SIMD)
+template <typename T, int TX, int TY, bool FIELD>
+__global__ TILE_BOUNDS(TX* TY, 2) void k_flat_batch(const Inst<T>* __restrict__ insts, const TileBlock* __restrict__ blocks,
+                                                    const T* __restrict__ fin, const T* __restrict__ forces,
+                                                    T* __restrict__ fout, const long long* __restrict__ step0, long long step)
+{
+    __shared__ T lds[TILE_SLOTS * TX * TY];
+    const TileBlock k = blocks[xcd_order((int)blockIdx.x, (int)gridDim.x)];
+    const Inst<T>& P = insts[k.inst];
+    const long long k0 = *step0 + step;
+    const T* force = (FIELD && forces && P.foff >= 0) ? forces + P.foff : nullptr;
+    fin += P.off;
+    fout += P.off;
+    if (P.uni) tile_body<T, TX, TY, true, true, FIELD, false, false, false>(P, fin, force, fout, 0.0, k0, 1, k.bx, k.by, lds);
+    else tile_body<T, TX, TY, false, true, FIELD, false, false, false>(P, fin, force, fout, 0.0, k0, 1, k.bx, k.by, lds);
+}
+
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
@@ -442,8 +459,7 @@ void tile_grid(int nx, int ny, int shape, int steps, int* tiles_x, int* tiles_y)
 }
 
 // Time of a launch of `steps` steps on `tiles` tiles in microseconds, `walls` the
-// share of them that holds a wall on the CUs that have the most of those.  A launch costs
-// 4.5, a tile with its CU to itself 2.9 per step (latency; a spilling wall body
+// share of them that holds a wall where the CUs have most of those.  A launch costs 4.5, a tile with its CU to itself 2.9 per step (latency; a spilling wall body
 // 6.5), and a CU with several tiles what follows for each.  Fitted on MI355X
 // to meshes of 40 x 20 to 2048^2, 10^6 x 1 to 65536 x 64 and 16 x 65536 cells and
 // 1 to 6 steps a launch (1024^2: 32.6, 27.1 and 29.8 us a step for 1, 2 and 3
@@ -469,8 +485,9 @@ static double tile_us(int shape, int steps, bool alone, double tiles, double wal
 // 82 -> 40 (55), 65536 x 64 254 -> 164 (177), 16384 x 128 109 -> 92 (101).  Between
 // near equals (3 % in steps, 7 % in shape, the fit's errors) the fewer steps and
 // the taller tiles stay.  The results do not depend on the choice.
-// (32 x 16 alone: up to one tile per CU, where no more waves come; 32 x 8 and 32 x 6
-// have no other form: without walls the 64 x 4 and 32 x 16 tiles are better.)
+// (32 x 16 alone: up to one tile per CU, where no more waves come.  32 x 8 and 32 x 6
+// have no other form: a wall-free one would take 10 to 15 % less on periodic
+// meshes of three rows and more.)
 static TilePick tile_pick(int nx, int ny, bool wall_x, bool wall_y, int most, int n_cu)
 {
     TilePick best;
@@ -576,46 +593,73 @@ int tile_run(dugks_ctx* ctx, void* f_a, void* f_b, const void* force, double t0,
     return DUGKS_OK;
 }
 
-// steps per launch of a batch of n instances of nx[i] x ny[i] cells
-int tile_batch_steps(int n, const int* nx, const int* ny, int n_cu)
+// Shape and steps per launch of a batch of n instances of nx[i] x ny[i] cells, with
+// walls across x (walls[i] & 1) and y (& 2), as tile_pick; wall tiles lie
+// between others here, so their mean share counts.  us a step, 32 x 16 tiles against
+// the choice (marched rows before both): 64 of 4096 x 2 cells, cavities 145 -> 32
+// (43), periodic 77 -> 29 (40); 64 of 4096 x 4, cavities with a field 211 -> 58
+// (98); 16 of 4096 x 16, cavities 73 -> 44 (61); 56 cavities of 28 to 460 cells a
+// side 83 -> 65 (211).
+TilePick tile_batch_pick(int n, const int* nx, const int* ny, const unsigned char* walls, int n_cu)
 {
-    int best = 1;
+    TilePick best;
     double best_us = 1e300;
-    for (int s = 1; s <= TILE_MAX_STEPS; ++s) {
-        long long t = 0;
-        for (int i = 0; i < n; ++i) {
-            int tx, ty;
-            tile_grid(nx[i], ny[i], 0, s, &tx, &ty);
-            t += (long long)tx * ty;
+    for (int shape = 0; shape < TILE_SHAPES; ++shape)
+        for (int s = 1; s <= (shape == 0 ? TILE_MAX_STEPS : 1); ++s) {
+            double tiles = 0, at_walls = 0;
+            for (int i = 0; i < n; ++i) {
+                int tx, ty;
+                tile_grid(nx[i], ny[i], shape, s, &tx, &ty);
+                const int fx = (walls[i] & 1) ? std::max(0, tx - 2) : tx, fy = (walls[i] & 2) ? std::max(0, ty - 2) : ty;
+                tiles += (double)tx * ty;
+                at_walls += (double)tx * ty - (double)fx * fy;
+            }
+            const double us = tile_us(shape, s, shape != 0, tiles, at_walls / tiles, n_cu) / s;
+            if (us < (shape == 0 ? 0.97 : best.shape == 0 ? 0.93 : 1.0) * best_us) {
+                best_us = us;
+                best.shape = shape, best.steps = s;
+            }
         }
-        const double us = tile_us(0, s, false, (double)t, 0.0, n_cu) / s;
-        if (us < best_us) {
-            best_us = us;
-            best = s;
-        }
-    }
     return best;
 }
 
 // `steps` steps of every instance; blocks: the nblocks workgroups of a launch of
-// `steps` steps.  (In parts where they are many: a launch holds less than 2^32
-// threads.)
-hipError_t tile_batch_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
-                             const void* forces, void* fout, const long long* step0, long long step, int steps,
-                             hipStream_t st)
+// `steps` steps on tiles of shape `shape`.  (In parts where they are many: a launch
+// holds less than 2^32 threads.)
+template <typename K, typename... Args>
+static hipError_t batch_parts(K kern, int threads, const void* insts, const TileBlock* blocks, long long nblocks,
+                              const void* fin, const void* forces, void* fout, const long long* step0, hipStream_t st,
+                              Args... args)
 {
-    constexpr int NT = TILES[0][0] * TILES[0][1];
-    constexpr long long PART = 1LL << 22;
-    static_assert(PART * NT < (1LL << 32), "threads of a launch");
-    auto kern = forces ? k_tile_batch<double, true> : k_tile_batch<double, false>;
+    constexpr long long PART = 1LL << 22;  // of at most 512 threads
     for (long long b = 0; b < nblocks; b += PART) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)std::min(PART, nblocks - b)), dim3(NT), 0, st,
+        hipLaunchKernelGGL(kern, dim3((unsigned)std::min(PART, nblocks - b)), dim3(threads), 0, st,
                            (const Inst<double>*)insts, blocks + b, (const double*)fin, (const double*)forces,
-                           (double*)fout, step0, step, steps);
+                           (double*)fout, step0, args...);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+template <int SHAPE>
+static hipError_t flat_launch(const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
+                              const void* forces, void* fout, const long long* step0, long long step, hipStream_t st)
+{
+    constexpr int TX = TILES[SHAPE][0], TY = TILES[SHAPE][1];
+    auto kern = forces ? k_flat_batch<double, TX, TY, true> : k_flat_batch<double, TX, TY, false>;
+    return batch_parts(kern, TX * TY, insts, blocks, nblocks, fin, forces, fout, step0, st, step);
+}
+
+hipError_t tile_batch_launch(int shape, const void* insts, const TileBlock* blocks, long long nblocks, const void* fin,
+                             const void* forces, void* fout, const long long* step0, long long step, int steps,
+                             hipStream_t st)
+{
+    if (shape == 1) return flat_launch<1>(insts, blocks, nblocks, fin, forces, fout, step0, step, st);
+    if (shape == 2) return flat_launch<2>(insts, blocks, nblocks, fin, forces, fout, step0, step, st);
+    if (shape == 3) return flat_launch<3>(insts, blocks, nblocks, fin, forces, fout, step0, step, st);
+    auto kern = forces ? k_tile_batch<double, true> : k_tile_batch<double, false>;
+    return batch_parts(kern, TILES[0][0] * TILES[0][1], insts, blocks, nblocks, fin, forces, fout, step0, st, step, steps);
 }
 
 }  // namespace dugks
