@@ -242,7 +242,8 @@ int dugks_velocity_change(dugks_ctx* ctx, const void* f_a, const void* f_b, cons
  *   lam_n       = (d f_{n+1} / d f_n)^T lam_np1
  *   grad_force += (d f_{n+1} / d G^)^T lam_np1   (nullable, [D])
  * The forward intermediates are recomputed from f_n (no tape).  In FP64
- * D2Q9 takes one launch over cell tiles and no scratch, D3Q19 three launches
+ * D2Q9 takes one launch over cell tiles and no scratch (thin meshes the
+ * passes below, where their scratch can be had), D3Q19 three launches
  * (f-bar-plus, faces, cells; wall axes of at least four cells, up to about
  * 28 million cells) with 4 Q + 9 values of scratch per cell.  Otherwise fully
  * periodic meshes take a gather form: in 2-D two launches over cell tiles

@@ -68,7 +68,8 @@ __device__ __forceinline__ Partials<LAT, T> partials(int q, T rho, const T* u, c
     return r;
 }
 
-// adjoint_tile.hip: one step of D2Q9 in FP64
+// adjoint_tile.hip: one step of D2Q9 in FP64, and the time it takes
+double adjoint_tile_us(const Inst<double>& P, int n_cu);
 void adjoint_tile_launch(const Inst<double>* Pd, const Inst<double>& P, const void* f, const void* force, double gt,
                          double gth, const void* lam, void* lam_out, void* grad, int n_cu, hipStream_t st);
 
@@ -1410,6 +1411,50 @@ void release_adjoint(dugks_ctx* ctx)
 using namespace dugks;
 
 namespace dugks {
+// What D2Q9 in FP64 takes: the one launch on tiles, or the passes above.  On meshes of
+// a few columns most lanes of a tile are halo, and on very long periodic ones of
+// five or six rows half of them.  The passes' time, fitted: general ones 25 us and
+// 0.2 per thousand cells of the ghost-extended grid + 0.35 per thousand of the
+// mesh, of that 0.7 while their scratch fits the cache, walls across x 8 % more;
+// periodic ones 14 us and, for every eight rows or part of them, 0.37 + 0.1 a row
+// per thousand columns, a third more beyond the cache (there tiles take a tenth
+// more; on few columns, an eighth less than modelled).  us a step, tiles against
+// passes: y walls, 1 x 65536 cells 185, 67; 4 x 65536 190, 143; 5 x 65536 186, 178;
+// 6 x 65536 189, 213; walls around, 2 x 16384 84, 45; 6 x 65536 301, 238; 8 x 65536
+// 302, 314; periodic, 4 x 65536 182, 124 (general); 65536 x 5 81, 70; 65536 x 7 83, 81.
+enum { ADJ2_TILES, ADJ2_PERIODIC, ADJ2_GENERAL };
+static int adjoint_2d_route(const Inst<double>& P, bool periodic, int n_cu)
+{
+    const bool far = P.nc > 600000;
+    double best = (P.n[0] <= 14 && P.per[0] ? 0.88 : periodic && far ? 1.1 : 1.0) * adjoint_tile_us(P, n_cu);
+    int route = ADJ2_TILES;
+    const double cells = 1e-3 * (0.2 * (double)P.ne + 0.35 * (double)P.nc);
+    const double general = (P.per[0] ? 1.04 : 1.12) * (25.0 + cells - 0.3 * std::min(cells, 180.0));
+    if (general < best) {
+        best = general;
+        route = ADJ2_GENERAL;
+    }
+    if (periodic) {
+        const int full = P.n[1] / 8, part = P.n[1] % 8;
+        const double cols = 1e-3 * ((P.n[0] + 31) / 32 * 32), us = cols * (full * 1.17 + (part ? 0.37 + 0.1 * part : 0.0));
+        if (1.05 * (14.0 + (far ? 1.35 : 1.0) * us) < best) route = ADJ2_PERIODIC;
+    }
+    return route;
+}
+
+// can the passes have `need` bytes of scratch?  (not allocated inside a capture)
+static bool adjoint_scratch_ready(dugks_ctx* ctx, size_t need, bool stat, hipStream_t st)
+{
+    if (stat) return need <= kStaticScratchBytes;
+    if (ctx->adj_bytes >= need) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+    void* unused = nullptr;
+    if (adjoint_scratch(ctx, need, false, &unused) == DUGKS_OK) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 // checks and kernel choice shared by dugks_step_adjoint and its
 // allocation-free variant (stat: scratch in the static area)
 static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, double t_n, const void* lam_np1,
@@ -1428,14 +1473,23 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
     const char* env = getenv("DUGKS_ADJOINT_GENERAL");
     const bool general = env && env[0] == '1';
     const bool d2 = ctx->cfg.lattice == DUGKS_D2Q9, f64 = ctx->cfg.dtype == DUGKS_F64;
-    // D2Q9 in FP64: one launch on tiles, no scratch; the allocation-free entry
-    // point keeps the sizes it takes.  FP32 stays on the passes below: its
-    // rounding is part of what callers compare.
-    if (d2 && f64 && !general) {
+    // D2Q9 in FP64: one launch on tiles, no scratch (thin meshes: the passes below,
+    // if their scratch can be had); the allocation-free entry point keeps the sizes
+    // it takes.  FP32 stays on the passes: its rounding is part of what callers compare.
+    int route = ADJ2_TILES;
+    size_t need2 = 0;
+    if (d2 && f64) {
+        const size_t need_general = adjoint_walls_bytes<D2Q9, double>(ctx->pd);
+        need2 = periodic ? adjoint_bytes<D2Q9, double>(ctx->pd) : need_general;
+        route = general ? (int)ADJ2_GENERAL : adjoint_2d_route(ctx->pd, periodic, ctx->n_cu);
+        if (!general && route != ADJ2_TILES &&
+            !adjoint_scratch_ready(ctx, route == ADJ2_GENERAL ? need_general : need2, stat, st))
+            route = ADJ2_TILES;
+    }
+    if (d2 && f64 && route == ADJ2_TILES) {
         if (stat) {
             void* unused = nullptr;
-            const int rc = adjoint_scratch(ctx, periodic ? adjoint_bytes<D2Q9, double>(ctx->pd)
-                                                         : adjoint_walls_bytes<D2Q9, double>(ctx->pd), true, &unused);
+            const int rc = adjoint_scratch(ctx, need2, true, &unused);
             if (rc != DUGKS_OK) return rc;
         }
         adjoint_tile_launch((const Inst<double>*)ctx->inst_dev, ctx->pd, f_n, force, tfac(ctx->pd, t_n),
@@ -1457,7 +1511,7 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
     }
     // meshes with walls: the general reverse pass (also taken on periodic
     // meshes when DUGKS_ADJOINT_GENERAL=1, to cross-check it)
-    if (!periodic || general) {
+    if (!periodic || general || route == ADJ2_GENERAL) {
         if (d2) {
             if (f64)
                 return adjoint_step_walls<D2Q9, double>(ctx, ctx->pd, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
@@ -1467,6 +1521,7 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
             return adjoint_step_walls<D3Q19, double>(ctx, ctx->pd, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
         return adjoint_step_walls<D3Q19, float>(ctx, ctx->pf, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
     }
+    if (d2 && f64) return adjoint_step<D2Q9, double>(ctx, ctx->pd, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
     if (d2) return adjoint_step<D2Q9, float>(ctx, ctx->pf, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
     if (f64) return adjoint_step<D3Q19, double>(ctx, ctx->pd, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);
     return adjoint_step<D3Q19, float>(ctx, ctx->pf, f_n, force, t_n, lam_np1, lam_n, grad_force, st, stat);

@@ -29,6 +29,8 @@
 // walls, stretched: 39 us (five launches) -> 13.2.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "ctx.hpp"
 #include "march.hpp"
 #include "wave.hpp"
@@ -38,7 +40,7 @@ namespace dugks {
 namespace {
 
 constexpr int A2_X = 32, A2_HALO = 2, A2_OX = A2_X - 2 * A2_HALO;
-// tile rows: on many cells, and on few (see adjoint_tile_us)
+// tile rows: on many cells, and on few (see adjoint_rows_us)
 constexpr int A2_ROWS = 16, A2_FEW = 8;
 
 // LDS planes of one value per lane: phi (e_y != 0, and the rest velocity), lam
@@ -512,28 +514,42 @@ __global__ __attribute__((amdgpu_flat_work_group_size(A2_X * A2_Y, A2_X * A2_Y),
     }
 }
 
-// Time of a launch in microseconds by tile rows (periodic meshes; walls add 4
-// to both): 16 rows, one workgroup per CU: 10.1 a round; 8 rows, two per CU: 7.6
-// while no CU has two, else 1.2 + 8.6 a round.  Measured, 8 against 16 rows:
-// 128^2 7.6, 10.1; 200 x 150 9.8, 10.4; 256^2 15.0, 11.0; 300^2 18.0, 19.2; 512^2
-// 42.9, 40.3.
-static double adjoint_tile_us(int rows, long long tiles, int n_cu)
+static long long adjoint_tiles(const Inst<double>& P, int rows)
 {
-    const long long cu = n_cu > 0 ? n_cu : 1;
-    if (rows == A2_ROWS) return 10.1 * (double)((tiles + cu - 1) / cu);
-    return tiles <= cu ? 7.6 : 1.2 + 8.6 * (double)((tiles + 2 * cu - 1) / (2 * cu));
+    const int oy = rows - 2 * A2_HALO;
+    return (long long)((P.n[0] + A2_OX - 1) / A2_OX) * ((P.n[1] + oy - 1) / oy);
+}
+
+// Time of a launch in microseconds by tile rows: 16 rows, one workgroup per CU: 10.1 a
+// round, 14.1 with walls; 8 rows, two per CU: 7.6 (11.6) while no CU has two,
+// else 1.2 + 8.6 (12.6) a round.  Measured on periodic meshes, 8 against 16 rows:
+// 128^2 7.6, 10.1; 200 x 150 9.8, 10.4; 256^2 15.0, 11.0; 300^2 18.0, 19.2; 512^2
+// 42.9, 40.3.  (walls: the share of the tiles that holds one where an XCD has most
+// of them)
+static double adjoint_rows_us(const Inst<double>& P, int rows, int n_cu)
+{
+    const long long cu = n_cu > 0 ? n_cu : 1, tiles = adjoint_tiles(P, rows);
+    const double tx = (P.n[0] + A2_OX - 1) / A2_OX, ty = (double)tiles / tx;
+    const double fx = P.per[0] ? 1.0 : std::max(0.0, 1.0 - 2.0 / tx), fy = P.per[1] ? 1.0 : std::max(0.0, 1.0 - 8.0 / ty);
+    const double w = 4.0 * (1.0 - fx * fy);
+    if (rows == A2_ROWS) return (10.1 + w) * (double)((tiles + cu - 1) / cu);
+    return tiles <= cu ? 7.6 + w : 1.2 + (8.6 + w) * (double)((tiles + 2 * cu - 1) / (2 * cu));
+}
+
+double adjoint_tile_us(const Inst<double>& P, int n_cu)
+{
+    return std::min(adjoint_rows_us(P, A2_ROWS, n_cu), adjoint_rows_us(P, A2_FEW, n_cu));
 }
 
 void adjoint_tile_launch(const Inst<double>* Pd, const Inst<double>& P, const void* f, const void* force, double gt,
                          double gth, const void* lam, void* lam_out, void* grad, int n_cu, hipStream_t st)
 {
     const int tiles_x = (P.n[0] + A2_OX - 1) / A2_OX;
-    auto tiles = [&](int rows) { return (long long)tiles_x * ((P.n[1] + rows - 2 * A2_HALO - 1) / (rows - 2 * A2_HALO)); };
     auto launch = [&](auto kern, int rows) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)tiles(rows)), dim3(A2_X * rows), 0, st, Pd, (const double*)f,
+        hipLaunchKernelGGL(kern, dim3((unsigned)adjoint_tiles(P, rows)), dim3(A2_X * rows), 0, st, Pd, (const double*)f,
                            (const double*)force, (const double*)lam, gt, gth, tiles_x, (double*)lam_out, (double*)grad);
     };
-    if (adjoint_tile_us(A2_FEW, tiles(A2_FEW), n_cu) < adjoint_tile_us(A2_ROWS, tiles(A2_ROWS), n_cu))
+    if (adjoint_rows_us(P, A2_FEW, n_cu) < adjoint_rows_us(P, A2_ROWS, n_cu))
         launch(k_adj2<double, A2_FEW>, A2_FEW);
     else
         launch(k_adj2<double, A2_ROWS>, A2_ROWS);

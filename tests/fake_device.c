@@ -78,6 +78,7 @@ hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, int a, int d) { *v = 256; return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
 hipError_t hipStreamSynchronize(void* s) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(void* s, int* c) { *c = 0; return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void* f, int a, int v) { return hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, int b, size_t l) { *n = 2; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void* s) { static char area[8]; *p = area; return hipSuccess; }
