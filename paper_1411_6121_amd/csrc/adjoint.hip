@@ -1471,7 +1471,9 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
         if (ctx->cfg.bc[s] != DUGKS_PERIODIC) periodic = false;
     const hipStream_t st = (hipStream_t)stream;
     const char* env = getenv("DUGKS_ADJOINT_GENERAL");
-    const bool general = env && env[0] == '1';
+    // to cross-check them: 1 the general reverse pass on every mesh, 2 the passes of a
+    // mesh's kind (periodic, or with walls), instead of the launches made for FP64
+    const bool general = env && env[0] == '1', passes = env && env[0] == '2';
     const bool d2 = ctx->cfg.lattice == DUGKS_D2Q9, f64 = ctx->cfg.dtype == DUGKS_F64;
     // D2Q9 in FP64: one launch on tiles, no scratch (thin meshes: the passes below,
     // if their scratch can be had); the allocation-free entry point keeps the sizes
@@ -1481,8 +1483,11 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
     if (d2 && f64) {
         const size_t need_general = adjoint_walls_bytes<D2Q9, double>(ctx->pd);
         need2 = periodic ? adjoint_bytes<D2Q9, double>(ctx->pd) : need_general;
-        route = general ? (int)ADJ2_GENERAL : adjoint_2d_route(ctx->pd, periodic, ctx->n_cu);
-        if (!general && route != ADJ2_TILES &&
+        route = general                ? (int)ADJ2_GENERAL
+                : passes && periodic ? (int)ADJ2_PERIODIC
+                : passes             ? (int)ADJ2_GENERAL
+                                     : adjoint_2d_route(ctx->pd, periodic, ctx->n_cu);
+        if (!general && !passes && route != ADJ2_TILES &&
             !adjoint_scratch_ready(ctx, route == ADJ2_GENERAL ? need_general : need2, stat, st))
             route = ADJ2_TILES;
     }
@@ -1498,7 +1503,7 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
     }
     // D3Q19 in FP64: three launches over the cells, with less scratch than the
     // passes below (the allocation-free entry point keeps the sizes it takes)
-    if (!d2 && f64 && !general && adjoint_cells_fit(ctx->pd)) {
+    if (!d2 && f64 && !general && !passes && adjoint_cells_fit(ctx->pd)) {
         const size_t need = !stat      ? adjoint_cells_bytes(ctx->pd)
                             : periodic ? adjoint_bytes<D3Q19, double>(ctx->pd)
                                        : adjoint_walls_bytes<D3Q19, double>(ctx->pd);
@@ -1509,8 +1514,7 @@ static int step_adjoint_any(dugks_ctx* ctx, const void* f_n, const void* force, 
                              tfac(ctx->pd, t_n + 0.5 * (double)ctx->cfg.dt), lam_np1, lam_n, grad_force, st);
         return hip_check(ctx, hipGetLastError(), "adjoint launch");
     }
-    // meshes with walls: the general reverse pass (also taken on periodic
-    // meshes when DUGKS_ADJOINT_GENERAL=1, to cross-check it)
+    // meshes with walls: the general reverse pass
     if (!periodic || general || route == ADJ2_GENERAL) {
         if (d2) {
             if (f64)
