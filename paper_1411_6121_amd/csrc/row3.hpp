@@ -39,6 +39,15 @@ namespace dugks {
 
 constexpr int ROW_X = 16;  // columns of a tile row: the DPP row of a wave
 
+// a value that every lane holds, in scalar registers: four vector registers that
+// the bodies with an acceleration spilled in their loops (128^3 periodic 326 ->
+// 298 us a step)
+__device__ __forceinline__ double uniform(double v)
+{
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b), hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
 template <typename T>
 __device__ __forceinline__ T row_next(T v) { return row_shift<1>(v); }
 template <typename T>
@@ -257,8 +266,8 @@ __device__ __forceinline__ T r3_recon(int e, T w, T k, T psL, T psR, T phL, T ph
 // One workgroup's work: tile `tile` (of tiles0 along x) and march chunk `ck`
 // of instance P.  ACC: there is an acceleration; FIELD: part of it is a force
 // field (force may be null: a batch where only some instances have one); NW:
-// the tile and chunk touch no wall.
-template <class LAT, typename T, int BY, bool UNI, bool ACC, bool FIELD, bool ORIG, bool NW>
+// the tile and chunk touch no wall; LOW: the chunk may begin at a low z wall.
+template <class LAT, typename T, int BY, bool UNI, bool ACC, bool FIELD, bool ORIG, bool NW, bool LOW>
 __device__ __forceinline__ void row_body(const Inst<T>& P, const T* __restrict__ fin, const T* __restrict__ force,
                                          T* __restrict__ fout, T gt, T gth, int chunk, int tiles0, int tile, int ck,
                                          T* lds)
@@ -397,13 +406,13 @@ __device__ __forceinline__ void row_body(const Inst<T>& P, const T* __restrict__
         for (int k = 0; k < K; ++k)
             if (LAT::e(k, 1) != 0) phi_at(b, k, cbase) = phi[k];
     };
-    // Planes arrive one after the other: p0 - 1, p0, .., p1.  Beyond a wall lies
-    // a ghost plane, extrapolated from the two planes that arrived last; at the
-    // low wall planes 0 and 1 arrive first (for it and for the interface
-    // opposite the wall), then the ghost plane, 0, 1, ..
-    const bool low = !NW && !perz && p0 == 0;
-    const int prime = low ? 4 : 2;  // arrivals before the first update
-    auto plane_at = [&](int i) { return p0 + 1 - prime + i + (low && i < 2 ? 3 : 0); };
+    // Planes arrive one after the other: p0 - 1, p0, .., p1.  Beyond the high wall
+    // lies a ghost plane, extrapolated from the two planes that arrived last.  At
+    // the low wall the march starts with plane 1: what plane 0 needs from below is
+    // formed before it, from planes 0 and 1.
+    const bool low = LOW && !perz && p0 == 0;
+    const int prime = 2;  // arrivals before the first update
+    auto plane_at = [&](int i) { return p0 - 1 + i; };
     // phi of the plane before the one that arrives is C, of the one before that
     // M (the e_z != 0 part; all of it at walls); X and Y of C; the z interface
     // below C; the entering values of the NEQ rule of a z wall.  The e_y != 0 part
@@ -418,28 +427,22 @@ __device__ __forceinline__ void row_body(const Inst<T>& P, const T* __restrict__
                       T (&XN)[K], T (&YN)[K], T (&fN)[K], T& rN) {
         const int p = plane_at(i);
         const bool full = i >= prime;  // plane p - 1 is updated
-        const bool ghost = !NW && !perz && (p == nz || p == -1);
+        const bool ghost = !NW && !perz && p == nz;
         RowCoef<T> m = row_coef<T, UNI>(P, 2, plane_of(p - 1), p < 0 ? 0 : p, sg);
         T acc[K], fp[K], fpr = T(0), gP[3] = {T(0), T(0), T(0)};  // fluxes; f~+ of Eq. (f_tilde_+)
         // a: f-bar-plus of plane p
         if (ghost) {
-            // beyond plane x with plane y inside: C and M at the high wall, M
-            // and C at the low one
-            const T q = p < 0 ? P.rlo[2] : P.rhi[2];
+            // beyond C with M inside
+            const T q = P.rhi[2];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if (LAT::e(k, 1) != 0) phC[k] = phi_at(buf ^ 1, k, cbase);
-                const T x = p < 0 ? phM[k] : phC[k], y = p < 0 ? phC[k] : phM[k];
-                phN[k] = fma_(q, y - x, x);
+                phN[k] = fma_(q, phM[k] - phC[k], phC[k]);
             }
-            const T x = p < 0 ? prM : prC, y = p < 0 ? prC : prM;
-            prN = fma_(q, y - x, x);
+            prN = fma_(q, prM - prC, prC);
             if constexpr (FIELD) {
 #pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const T gx_ = p < 0 ? gM[d] : gC[d], gy_ = p < 0 ? gC[d] : gM[d];
-                    gN[d] = fma_(q, gy_ - gx_, gx_);
-                }
+                for (int d = 0; d < 3; ++d) gN[d] = fma_(q, gM[d] - gC[d], gC[d]);
             }
         } else {
             make_phi(fN, rN, gN, phN, prN);
@@ -512,7 +515,7 @@ __device__ __forceinline__ void row_body(const Inst<T>& P, const T* __restrict__
         for (int k = 0; k < K; ++k)
             if (LAT::e(k, 1) != 0) phN[k] = phi_at(buf, k, cbase);
         make_xy(buf, phN, XN, YN);
-        if (low ? (i == 1 || i >= 3) : i >= 1) {
+        if (i >= 1) {
             T v[K], r, G[3];
 #pragma unroll
             for (int k = 0; k < K; ++k)
@@ -520,11 +523,9 @@ __device__ __forceinline__ void row_body(const Inst<T>& P, const T* __restrict__
                                         phN[k]);
             r = r3_recon<T, UNI>(0, m.w, m.k, prC, prN, prC, prN);
             face_acc(gC, gN, m.w, G);
-            const bool wl = low && i == 3, wh = !NW && !perz && p == nz;
-            if (wl || wh) r3_wall<LAT, T, 2>(P, wl ? 4 : 5, wl ? 1 : -1, v, zW, sg);
+            if (ghost) r3_wall<LAT, T, 2>(P, 5, -1, v, zW, sg);
             const EqR<T> E = r3_point<LAT, T, ORIG, ACC>(P, v, r, sg, G, hh);
-            const bool ol = low && i == 1, oh = !NW && !perz && p == nz - 1;
-            if (ol || oh) r3_enter<LAT, T, 2, ORIG>(P, ol ? 4 : 5, E, v, sg, gth, zW);
+            if (!NW && !perz && p == nz - 1) r3_enter<LAT, T, 2, ORIG>(P, 5, E, v, sg, gth, zW);
 #pragma unroll
             for (int k = 0; k < K; ++k)
                 if (LAT::e(k, 2) != 0) zlo[k] = r3_relax<LAT, T, ACC>(E, k, P.B7, P.C7, v[k]);
@@ -649,12 +650,58 @@ __device__ __forceinline__ void row_body(const Inst<T>& P, const T* __restrict__
     T phA[K], prA = T(0), XA[K], YA[K], fA[K], rA, phB[K], prB, XB[K], YB[K], fB[K], rB;
 #pragma unroll
     for (int k = 0; k < K; ++k) phA[k] = XA[k] = YA[k] = fA[k] = T(0);
-    load_plane(plane_at(0), fB, rB, gN);
+    const int i0 = low ? 2 : 0;
+    load_plane(plane_at(i0), fB, rB, gN);
+    if constexpr (LOW) {
+        if (low) {
+            // planes 0 and 1, the interface between them and from it the wall's
+            // face, whose ghost plane is extrapolated (psi too, as beside the rows
+            // at y walls): as many planes as a march inside the mesh primes.  With
+            // planes 0 and 1, the ghost plane, 0 and 1 as arrivals of the march, a
+            // 24 x 22 x 29 stretched cavity took 21.2 us a step, now 15.6 (19.4 on
+            // the LDS march before), 822 x 215 x 6 308, now 225 (274).
+            T ph1[K], pr1, X1[K], Y1[K], v[K], W[K], G[3], gl[3];
+            load_plane(0, fA, rA, gC);
+            make_phi(fA, rA, gC, phA, prA);
+            make_phi(fB, rB, gN, ph1, pr1);
+            to_lds(1, phA);
+            to_lds(0, ph1);
+            __syncthreads();
+            make_xy(1, phA, XA, YA);
+            make_xy(0, ph1, X1, Y1);
+            const RowCoef<T> m = row_coef<T, UNI>(P, 2, 0, 1, sg), m0 = row_coef<T, UNI>(P, 2, 0, 0, sg);
+            const T q = P.rlo[2];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                X1[k] = psi_z(k, ph1, X1, Y1);  // psi of the planes
+                Y1[k] = psi_z(k, phA, XA, YA);
+                v[k] = r3_recon<T, UNI>(LAT::e(k, 2), m.w, m.k, Y1[k], X1[k], phA[k], ph1[k]);
+            }
+            face_acc(gC, gN, m.w, G);
+            const EqR<T> E = r3_point<LAT, T, ORIG, ACC>(P, v, r3_recon<T, UNI>(0, m.w, m.k, prA, pr1, T(0), T(0)), sg, G, hh);
+            r3_enter<LAT, T, 2, ORIG>(P, 4, E, v, sg, gth, W);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                phM[k] = fma_(q, ph1[k] - phA[k], phA[k]);
+                v[k] = r3_recon<T, UNI>(LAT::e(k, 2), m0.w, m0.k, fma_(q, X1[k] - Y1[k], Y1[k]), Y1[k], phM[k], phA[k]);
+            }
+#pragma unroll
+            for (int d = 0; d < 3; ++d) gl[d] = fma_(q, gN[d] - gC[d], gC[d]);
+            face_acc(gl, gC, m0.w, G);
+            r3_wall<LAT, T, 2>(P, 4, 1, v, W, sg);
+            const EqR<T> B = r3_point<LAT, T, ORIG, ACC>(
+                P, v, r3_recon<T, UNI>(0, m0.w, m0.k, fma_(q, pr1 - prA, prA), prA, T(0), T(0)), sg, G, hh);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (LAT::e(k, 2) != 0) zlo[k] = r3_relax<LAT, T, ACC>(B, k, P.B7, P.C7, v[k]);
+            __syncthreads();
+        }
+    }
     // two arrivals per trip, so that no register is copied from set to set; the
     // wall body of D3Q19 has no registers left for it (spills: 375 -> 386 us a
     // step of the 128^3 cavity; D3Q27 at 96^3 363 -> 344 with it)
     if constexpr (NW || LAT::Q != 19) {
-        for (int i = 0;; i += 2) {
+        for (int i = i0;; i += 2) {
             arrive(i, phA, prA, XA, YA, fA, rA, phB, prB, XB, YB, fB, rB);
             if (i + 1 == count) break;
             arrive(i + 1, phB, prB, XB, YB, fB, rB, phA, prA, XA, YA, fA, rA);
@@ -662,7 +709,7 @@ __device__ __forceinline__ void row_body(const Inst<T>& P, const T* __restrict__
         }
     } else {
 #pragma unroll 1
-        for (int i = 0; i < count; ++i) {
+        for (int i = i0; i < count; ++i) {
             arrive(i, phA, prA, XA, YA, fA, rA, phB, prB, XB, YB, fB, rB);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -697,8 +744,10 @@ __device__ __forceinline__ bool row_no_wall(const Inst<T>& P, int BY, int tiles0
 }
 
 // Tile rows, and waves per SIMD the kernel is compiled for: the most that its
-// registers allow without spills (about 250 in D3Q19; one more wave spills and
-// runs 1.5 times as long).  Eight rows give workgroups of
+// registers allow.  D3Q19 at two takes 248 to 256 and spills none on uniform
+// meshes without a field, 2 to 21 on stretched ones, 24 to 52 with a field, 17 and
+// 71 in the batch's kernels (four bodies each); one more wave spills throughout
+// and runs 1.5 times as long.  Eight rows give workgroups of
 // four waves, two of which share a CU, so that one computes while
 // another waits at a barrier; 16 rows (one workgroup per CU) were slower in
 // spite of their smaller halo (128^3 periodic: 308 against 272 us).
@@ -755,19 +804,25 @@ __global__ ROW_BOUNDS(LAT, T) void k_row(const Inst<T>* __restrict__ Pp, const T
         gt = tfac_dev(P, t);
         gth = tfac_dev(P, t + 0.5 * P.dtd);
     }
+    gt = uniform(gt);
+    gth = uniform(gth);
     // the chunks at the z walls first, then the others, each part in XCD order:
-    // they take up to twice as long, and with all chunks in one order the first
-    // and the last XCD had nothing else (128^3 cavity 368 -> 336 us a step; bands
-    // of tiles with all their chunks per XCD: 355, but then the y walls sit on
-    // two XCDs, D3Q27 136 -> 150)
+    // every tile of theirs is on the wall body, and with all chunks in one order
+    // the first and the last XCD have nothing else (128^3 cavity 357 -> 336 us a
+    // step, 120 x 101 x 90 181 -> 176; bands of tiles with all their chunks per
+    // XCD gain as much there, but then the y walls sit on two XCDs, D3Q27 136 -> 150)
     const int nck = (P.n[2] + chunk - 1) / chunk, nb = (int)gridDim.x, wz = P.per[2] || nck < 3 ? 0 : 2 * tiles;
     const bool zw = (int)blockIdx.x < wz;
     const int b = zw ? xcd_order((int)blockIdx.x, wz) : xcd_order((int)blockIdx.x - wz, nb - wz);
     const int tile = b % tiles, ck = zw ? (b < tiles ? 0 : nck - 1) : b / tiles + (wz ? 1 : 0);
-    if (row_no_wall(P, BY, tiles0, tile, ck, chunk))
-        row_body<LAT, T, BY, UNI, ACC, FIELD, ORIG, true>(P, fin, force, fout, gt, gth, chunk, tiles0, tile, ck, lds);
-    else
-        row_body<LAT, T, BY, UNI, ACC, FIELD, ORIG, false>(P, fin, force, fout, gt, gth, chunk, tiles0, tile, ck, lds);
+    // D3Q19's wall body begins at a low wall by itself; D3Q27's has no registers
+    // left for that (75 x 66 x 50: 124 us a step, 120 with a body of its own)
+#define DUGKS_ROW(NW, LOW) \
+    row_body<LAT, T, BY, UNI, ACC, FIELD, ORIG, NW, LOW>(P, fin, force, fout, gt, gth, chunk, tiles0, tile, ck, lds)
+    if (row_no_wall(P, BY, tiles0, tile, ck, chunk)) DUGKS_ROW(true, false);
+    else if (LAT::Q == 19 || (!P.per[2] && ck == 0)) DUGKS_ROW(false, true);
+    else if constexpr (LAT::Q != 19) DUGKS_ROW(false, false);
+#undef DUGKS_ROW
 }
 
 template <class LAT, typename T, bool UNI, bool ACC, bool FIELD, bool ORIG>
@@ -821,17 +876,17 @@ __global__ ROW_BOUNDS(LAT, T) void k_row_batch(const Inst<T>* __restrict__ insts
     const int local = (int)(b - bstart[lo]), ntile = g.tiles0 * g.tiles1;
     const int tile = local % ntile, ck = local / ntile;
     const double t = (double)(*step0 + step) * P.dtd;
-    const T gt = tfac_dev(P, t), gth = tfac_dev(P, t + 0.5 * P.dtd);
+    const T gt = uniform(tfac_dev(P, t)), gth = uniform(tfac_dev(P, t + 0.5 * P.dtd));
     const T* force = (FIELD && forces && P.foff >= 0) ? forces + P.foff : nullptr;
     const bool nw = row_no_wall(P, BY, g.tiles0, tile, ck, g.chunk);
     fin += P.off;
     fout += P.off;
     if (P.uni) {
-        if (nw) row_body<LAT, T, BY, true, true, FIELD, false, true>(P, fin, force, fout, gt, gth, g.chunk, g.tiles0, tile, ck, lds);
-        else row_body<LAT, T, BY, true, true, FIELD, false, false>(P, fin, force, fout, gt, gth, g.chunk, g.tiles0, tile, ck, lds);
+        if (nw) row_body<LAT, T, BY, true, true, FIELD, false, true, false>(P, fin, force, fout, gt, gth, g.chunk, g.tiles0, tile, ck, lds);
+        else row_body<LAT, T, BY, true, true, FIELD, false, false, true>(P, fin, force, fout, gt, gth, g.chunk, g.tiles0, tile, ck, lds);
     } else {
-        if (nw) row_body<LAT, T, BY, false, true, FIELD, false, true>(P, fin, force, fout, gt, gth, g.chunk, g.tiles0, tile, ck, lds);
-        else row_body<LAT, T, BY, false, true, FIELD, false, false>(P, fin, force, fout, gt, gth, g.chunk, g.tiles0, tile, ck, lds);
+        if (nw) row_body<LAT, T, BY, false, true, FIELD, false, true, false>(P, fin, force, fout, gt, gth, g.chunk, g.tiles0, tile, ck, lds);
+        else row_body<LAT, T, BY, false, true, FIELD, false, false, true>(P, fin, force, fout, gt, gth, g.chunk, g.tiles0, tile, ck, lds);
     }
 }
 
