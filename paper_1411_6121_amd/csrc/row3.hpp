@@ -855,7 +855,11 @@ static int launch_row_acc(dugks_ctx* ctx, const Inst<T>& P, const void* fin, voi
 // many instances in one launch: workgroup b in XCD order belongs to the
 // instance i with bstart[i] <= b < bstart[i + 1], whose tile counts and chunk are
 // geom[i]; instance i is at time (*step0 + step) dt_i (a device counter, so a
-// captured graph replays with advancing time)
+// captured graph replays with advancing time).
+// Four bodies in one kernel spill more than a single mesh's (RowShape).  us a step,
+// LDS march with its own kernel -> this one: eight 40^3 boxes with walls 177 -> 127,
+// with a field 314 -> 149; it stays a little behind for few boxes of uneven sides,
+// where most tiles hold walls (two of 23 x 18 x 73: 53.3 -> 55.6)
 template <class LAT, typename T, bool FIELD>
 __global__ ROW_BOUNDS(LAT, T) void k_row_batch(const Inst<T>* __restrict__ insts, const long long* __restrict__ bstart,
                                                const BatchGeom* __restrict__ geom, int ninst,
