@@ -459,19 +459,21 @@ void tile_grid(int nx, int ny, int shape, int steps, int* tiles_x, int* tiles_y)
 }
 
 // Time of a launch of `steps` steps on `tiles` tiles in microseconds, `walls` the
-// share of them that holds a wall where the CUs have most of those.  A launch costs 4.5, a tile with its CU to itself 2.9 per step (latency; a spilling wall body
-// 6.5), and a CU with several tiles what follows for each.  Fitted on MI355X
-// to meshes of 40 x 20 to 2048^2, 10^6 x 1 to 65536 x 64 and 16 x 65536 cells and
-// 1 to 6 steps a launch (1024^2: 32.6, 27.1 and 29.8 us a step for 1, 2 and 3
-// steps; 128^2 cavity: 7.4, 4.8, 4.1, 3.8, 3.7 and 3.7 us for 1 to 6).
-static double tile_us(int shape, int steps, bool alone, double tiles, double walls, int n_cu)
+// share of them that holds a wall where the CUs have most of those.  A launch costs
+// 4.5, a tile with its CU to itself 2.9 per step (latency; a spilling wall body 6.5,
+// but 5.5 where no tile has `corners`, the wall code of both axes, and all run at
+// once, two per CU), and a CU with several tiles what follows for each.  Fitted
+// on MI355X to meshes of 40 x 20 to 2048^2, 10^6 x 1 to 65536 x 64 and 16 x 65536
+// cells and 1 to 6 steps a launch (1024^2: 32.6, 27.1 and 29.8 us a step for 1, 2
+// and 3 steps; 128^2 cavity: 7.4, 4.8, 4.1, 3.8, 3.7 and 3.7 us for 1 to 6).
+static double tile_us(int shape, int steps, bool alone, double tiles, double walls, bool corners, int n_cu)
 {
     const double cu = n_cu > 0 ? n_cu : 1, per_cu = std::ceil(tiles / cu), s = steps;
     // per tile of a CU that has several: without a wall, with one, all on the wall body
     static const double each[TILE_SHAPES][3] = {{0, 0, 0}, {0, 0, 1.40}, {0, 0, 1.15}, {1.15, 3.0, 1.5}};
     if (alone) return 4.5 + std::max(2.9 * s, shape == 0 ? 0.0 : per_cu * each[shape][2]);
     const double free_ = shape == 0 ? 1.5 + 1.25 * s : each[shape][0], wall = shape == 0 ? 3.5 + 2.9 * s : each[shape][1];
-    return 4.5 + std::max((walls > 0 ? 6.5 : 2.9) * s, per_cu * (free_ + walls * (wall - free_)));
+    return 4.5 + std::max((walls <= 0 ? 2.9 : corners || per_cu > 2 ? 6.5 : 5.5) * s, per_cu * (free_ + walls * (wall - free_)));
 }
 
 // How to take a mesh: the shape and steps per launch (at most `most`) of the
@@ -484,7 +486,9 @@ static double tile_us(int shape, int steps, bool alone, double tiles, double wal
 // 1 periodic 260 -> 72 (79), 10^6 x 2 cavity 642 -> 100 (121), 65536 x 16 cavity
 // 82 -> 40 (55), 65536 x 64 254 -> 164 (177), 16384 x 128 109 -> 92 (101).  Between
 // near equals (3 % in steps, 7 % in shape, the fit's errors) the fewer steps and
-// the taller tiles stay.  The results do not depend on the choice.
+// the taller tiles stay, and against 32 x 16 alone several steps have to be worth
+// 7 %, too.  Walls across one axis (one step alone against the choice): 3654 x 16
+// 8.9 -> 6.6, 450 x 200 7.3 -> 6.7.  The results do not depend on the choice.
 // (32 x 16 alone: up to one tile per CU, where no more waves come.  32 x 8 and 32 x 6
 // have no other form: a wall-free one would take 10 to 15 % less on periodic
 // meshes of three rows and more.)
@@ -501,8 +505,9 @@ static TilePick tile_pick(int nx, int ny, bool wall_x, bool wall_y, int most, in
             for (const bool alone : {false, true}) {
                 if (shape == 0 && alone && (tiles > n_cu || !(wall_x || wall_y))) continue;
                 if ((shape == 1 || shape == 2) && !alone) continue;
-                const double us = tile_us(shape, s, alone, tiles, walls, n_cu) / s;
-                if (us < (shape == 0 ? 0.97 : best.shape == 0 ? 0.93 : 1.0) * best_us) {
+                const double us = tile_us(shape, s, alone, tiles, walls, wall_x && wall_y, n_cu) / s;
+                const bool easy = shape == 0 ? alone || !best.alone : best.shape != 0;
+                if (us < (!easy ? 0.93 : shape == 0 ? 0.97 : 1.0) * best_us) {
                     best_us = us;
                     best.shape = shape, best.steps = s, best.alone = alone;
                 }
@@ -614,7 +619,7 @@ TilePick tile_batch_pick(int n, const int* nx, const int* ny, const unsigned cha
                 tiles += (double)tx * ty;
                 at_walls += (double)tx * ty - (double)fx * fy;
             }
-            const double us = tile_us(shape, s, shape != 0, tiles, at_walls / tiles, n_cu) / s;
+            const double us = tile_us(shape, s, shape != 0, tiles, at_walls / tiles, at_walls > 0, n_cu) / s;
             if (us < (shape == 0 ? 0.97 : best.shape == 0 ? 0.93 : 1.0) * best_us) {
                 best_us = us;
                 best.shape = shape, best.steps = s;
