@@ -485,10 +485,12 @@ static double tile_us(int shape, int steps, bool alone, double tiles, double wal
 // best steps against the choice (marched rows of 128 columns before both): 10^6 x
 // 1 periodic 260 -> 72 (79), 10^6 x 2 cavity 642 -> 100 (121), 65536 x 16 cavity
 // 82 -> 40 (55), 65536 x 64 254 -> 164 (177), 16384 x 128 109 -> 92 (101).  Between
-// near equals (3 % in steps, 7 % in shape, the fit's errors) the fewer steps and
-// the taller tiles stay, and against 32 x 16 alone several steps have to be worth
-// 7 %, too.  Walls across one axis (one step alone against the choice): 3654 x 16
-// 8.9 -> 6.6, 450 x 200 7.3 -> 6.7.  The results do not depend on the choice.
+// near equals (3 % in steps, the fit's errors) the fewer steps stay, several steps
+// have to be worth 7 % against 32 x 16 alone, and a flatter shape 10 % (at 7 %
+// 1024^2 cavities took 32 x 8 for single steps: plain 38 -> 38 us, but stretched 45 ->
+// 48, with a field 47 -> 50).  Walls across one axis (one step alone against the
+// choice): 3654 x 16 8.9 -> 6.6, 450 x 200 7.3 -> 6.7.  The results do not depend
+// on the choice.
 // (32 x 16 alone: up to one tile per CU, where no more waves come.  32 x 8 and 32 x 6
 // have no other form: a wall-free one would take 10 to 15 % less on periodic
 // meshes of three rows and more.)
@@ -507,7 +509,7 @@ static TilePick tile_pick(int nx, int ny, bool wall_x, bool wall_y, int most, in
                 if ((shape == 1 || shape == 2) && !alone) continue;
                 const double us = tile_us(shape, s, alone, tiles, walls, wall_x && wall_y, n_cu) / s;
                 const bool easy = shape == 0 ? alone || !best.alone : best.shape != 0;
-                if (us < (!easy ? 0.93 : shape == 0 ? 0.97 : 1.0) * best_us) {
+                if (us < (easy ? (shape == 0 ? 0.97 : 1.0) : shape == 0 ? 0.93 : 0.90) * best_us) {
                     best_us = us;
                     best.shape = shape, best.steps = s, best.alone = alone;
                 }
