@@ -622,8 +622,8 @@ int split_step(dugks_ctx* ctx, const void* fin, void* fout, const void* force, d
 // occupancy it is built for, which D3Q19 does on uniform meshes without a force
 // field only, else the one-lane march (2).  (FP64 takes the register kernels,
 // kernels_tile.hip and row3.hpp.  In FP32 they run 1.2 to 2 times as fast as
-// these as well, but round differently, and FP32 states and their totals are
-// kept bit for bit.)
+// these as well, but round differently, by FP32's own rounding.  That FP32 states
+// and their totals are kept bit for bit is a choice, no limit of speed.)
 static int default_f32_kernel(int lattice, bool uniform, bool field)
 {
     if (lattice == DUGKS_D2Q9 || lattice == DUGKS_D3Q27) return 3;

@@ -1,8 +1,9 @@
 // kernels_split.hip -- the fused single-launch step in FP32 with the velocity
 // set split over two lanes per column.  (In FP64 the row march of row3.hpp and
 // the tiles of kernels_tile.hip are 1.1 to 2.6 times as fast.  In FP32 they are
-// too, up to 2.1 times at 120 x 101 x 90, but round differently, by more than what
-// totals accumulated in FP64 from an FP32 state are compared to.)
+// too, up to 2.1 times at 120 x 101 x 90, but round differently, by FP32's own
+// rounding.  FP32 stays here so that its states and their FP64 totals keep their
+// bits; it is no limit of speed.)
 //
 // The march is that of the faces-once fused kernel (an LDS ring of three
 // f-bar-plus planes, every interface evaluated once, x/y face values
