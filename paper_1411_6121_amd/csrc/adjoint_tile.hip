@@ -40,7 +40,7 @@ namespace dugks {
 namespace {
 
 constexpr int A2_X = 32, A2_HALO = 2, A2_OX = A2_X - 2 * A2_HALO;
-// tile rows: on many cells, and on few (see adjoint_rows_us)
+// tile rows: on many cells, and on few (see adjoint_rows)
 constexpr int A2_ROWS = 16, A2_FEW = 8;
 
 // LDS planes of one value per lane: phi (e_y != 0, and the rest velocity), lam
@@ -526,19 +526,27 @@ static long long adjoint_tiles(const Inst<double>& P, int rows)
 // 128^2 7.6, 10.1; 200 x 150 9.8, 10.4; 256^2 15.0, 11.0; 300^2 18.0, 19.2; 512^2
 // 42.9, 40.3.  (walls: the share of the tiles that holds one where an XCD has most
 // of them)
-static double adjoint_rows_us(const Inst<double>& P, int rows, int n_cu)
+static double adjoint_rows_us(const Inst<double>& P, int rows, bool walls, int n_cu)
 {
     const long long cu = n_cu > 0 ? n_cu : 1, tiles = adjoint_tiles(P, rows);
     const double tx = (P.n[0] + A2_OX - 1) / A2_OX, ty = (double)tiles / tx;
     const double fx = P.per[0] ? 1.0 : std::max(0.0, 1.0 - 2.0 / tx), fy = P.per[1] ? 1.0 : std::max(0.0, 1.0 - 8.0 / ty);
-    const double w = 4.0 * (1.0 - fx * fy);
+    const double w = walls ? 4.0 * (1.0 - fx * fy) : 0.0;
     if (rows == A2_ROWS) return (10.1 + w) * (double)((tiles + cu - 1) / cu);
     return tiles <= cu ? 7.6 + w : 1.2 + (8.6 + w) * (double)((tiles + 2 * cu - 1) / (2 * cu));
 }
 
+// The rows of a launch, compared without walls, as the time of both kinds of tiles
+// grows alike: with each kind's own share 5035 x 54 inside walls takes 8 rows, 55
+// us against 46.
+static int adjoint_rows(const Inst<double>& P, int n_cu)
+{
+    return adjoint_rows_us(P, A2_FEW, false, n_cu) < adjoint_rows_us(P, A2_ROWS, false, n_cu) ? A2_FEW : A2_ROWS;
+}
+
 double adjoint_tile_us(const Inst<double>& P, int n_cu)
 {
-    return std::min(adjoint_rows_us(P, A2_ROWS, n_cu), adjoint_rows_us(P, A2_FEW, n_cu));
+    return adjoint_rows_us(P, adjoint_rows(P, n_cu), true, n_cu);
 }
 
 void adjoint_tile_launch(const Inst<double>* Pd, const Inst<double>& P, const void* f, const void* force, double gt,
@@ -549,7 +557,7 @@ void adjoint_tile_launch(const Inst<double>* Pd, const Inst<double>& P, const vo
         hipLaunchKernelGGL(kern, dim3((unsigned)adjoint_tiles(P, rows)), dim3(A2_X * rows), 0, st, Pd, (const double*)f,
                            (const double*)force, (const double*)lam, gt, gth, tiles_x, (double*)lam_out, (double*)grad);
     };
-    if (adjoint_rows_us(P, A2_FEW, n_cu) < adjoint_rows_us(P, A2_ROWS, n_cu))
+    if (adjoint_rows(P, n_cu) == A2_FEW)
         launch(k_adj2<double, A2_FEW>, A2_FEW);
     else
         launch(k_adj2<double, A2_ROWS>, A2_ROWS);
